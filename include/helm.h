@@ -84,7 +84,9 @@ typedef struct {
                                  HIP graph and replayed; 0: kernels are launched one by one */
     int32_t adr_levels;       /* levels of the ADR V-cycle, from level 2 down (default 3; 0 = all, L - 1) */
     int32_t tail_n;           /* a coarsest ADR level with at most tail_n nodes on its longer side (and at most
-                                 4096 nodes) runs its GMRES in one workgroup (default 64; 0 = never) */
+                                 4096 nodes) runs its GMRES in one workgroup (default 64; 0 = never).  Not
+                                 used where the ADR levels are joined across their Gram passes: GMRES(3)
+                                 in s-step form on every level, no tuned form, small grids */
     int32_t wave_tail_n;      /* the wave levels >= 3 with at most wave_tail_n nodes on the longer side run in
                                  one workgroup, all of them in a single launch (default 32; 0 = never) */
     double shift;             /* relative imaginary shift s0 >= 0 of the shifted equation (Section 4.3.2,

@@ -21,6 +21,7 @@
 
 #include "../../include/helm.h"
 #include "kernels_tail.hpp"
+#include "kernels_adrfuse.hpp"
 #include "kernels_adjoint.hpp"
 #include "kernels_wtail.hpp"
 #include "kernels_eik.hpp"
@@ -596,12 +597,137 @@ struct Engine {
         a.bout = (C*)bout;
         return a;
     }
+    // ---- ADR levels joined across their Gram passes (kernels_adrfuse.hpp)
+    // Levels l..LA run so: GMRES(3) on every one of them, none in a form set by a tuning, at
+    // least two levels, and level l of at most FUSE_FOLD tiles of 32 x 32 (one per CU; a
+    // larger level is bound by its arithmetic, of which the rings recompute up to 2.5 times).
+    bool fuse_levels(int l) const {
+        if (c->d.gmres_m != 3 || c->d.gmres_coarse_m != 3 || c->d.gmres_arnoldi || c->LA <= l) return false;
+        for (int q = l; q <= c->LA; ++q)
+            if (c->tn.sstep_rows[q] != 0) return false;
+        return fuse_tiles(c->al[l].nx, c->al[l].ny, 32) <= FUSE_FOLD;
+    }
+    // Tile edge of the kernels whose finer level is l: 16 x 16 while that gives at most one
+    // block per CU and partials that the consumers can sum (FUSE_FOLD), else 32 x 32.
+    int fuse_ft(int l) const { return fuse_tiles(c->al[l].nx, c->al[l].ny, 16) <= FUSE_FOLD ? 16 : 32; }
+    int fuse_ng(int l) const { return fuse_tiles(c->al[l].nx, c->al[l].ny, fuse_ft(l)); }
+    // The two halves of the reduction scratch that producers and consumers use in turn (the
+    // scratch holds 52 doubles for each of at least 2048 blocks).
+    double* fuse_part(int half) const { return c->partials + (size_t)half * 16 * FUSE_FOLD; }
+    // From the Gram sums of the pre-smoother on level l (fuse_ng(l) partials in half h) to
+    // those of its post-smoother (as many, in the half left in h); the iterate of level l
+    // ends in A.x.
+    void fuse_down_up(int l, int& h) {
+        int np = fuse_ng(l);  // partials of the last Gram sums
+        for (int q = l; q < c->LA; ++q) {
+            AdrLevel &A = c->al[q], &B = c->al[q + 1];
+            const double bytes = (3 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny) + (2 * sizeof(C) + 2 * sizeof(T)) * NN2(B.nx, B.ny);
+            with_edge(fuse_ft(q), [&](auto e) {
+                constexpr int FT = decltype(e)::value;
+                LAUNCH(c, bytes, (k_fuse_down<T, FT>), dim3(fuse_ng(q)), dim3(FuseCfg<FT>::DOWN), st, A.A, B.A,
+                       (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b, (const double*)fuse_part(h), np,
+                       (C*)A.x, (const T*)B.px, (const T*)B.py, (const C*)B.c0, (C*)B.b, fuse_part(1 - h));
+            });
+            np = fuse_ng(q);  // one per tile of the finer level
+            h = 1 - h;
+        }
+        for (int q = c->LA; q > l; --q) {
+            fuse_up<true>(q, np, h);
+            np = fuse_ng(q - 1);
+        }
+    }
+    // Level q finished and prolonged into level q - 1 (np Gram partials in half h): with GRAM
+    // into its other iterate, with the Gram sums of its post-smoother in the half left in h;
+    // else added in place to pinto.
+    template <bool GRAM>
+    void fuse_up(int q, int np, int& h, void* pinto = nullptr) {
+        AdrLevel &A = c->al[q - 1], &B = c->al[q];
+        const bool x0 = q < c->LA;
+        const double bytes = ((GRAM ? 4 : 2) * sizeof(C) + (GRAM ? 2 : 0) * sizeof(T)) * NN2(A.nx, A.ny) +
+                             ((x0 ? 3 : 2) * sizeof(C) + 2 * sizeof(T)) * NN2(B.nx, B.ny);
+        auto go = [&](auto xc, auto e) {
+            constexpr int FT = decltype(e)::value;
+            LAUNCH(c, bytes, (k_fuse_up<T, decltype(xc)::value, FT, GRAM>), dim3(fuse_tiles(A.nx, A.ny, FT)),
+                   dim3(FuseCfg<FT>::UP), st, A.A, B.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   (const C*)(GRAM ? A.x : pinto), (C*)(GRAM ? A.xalt : pinto), (const T*)B.px, (const T*)B.py,
+                   (const C*)B.c0, (const C*)B.b, (const C*)B.x, (const double*)fuse_part(h), np, fuse_part(1 - h));
+        };
+        with_edge(fuse_ft(q - 1), [&](auto e) {
+            if (x0)
+                go(std::true_type{}, e);
+            else
+                go(std::false_type{}, e);
+        });
+        if (GRAM) std::swap(A.x, A.xalt);
+        h = 1 - h;
+    }
+    void fuse_homes(void* const (&home)[16]) {
+        for (int q = 2; q <= c->LA && q < 16; ++q)
+            if (c->al[q].x != home[q]) std::swap(c->al[q].x, c->al[q].xalt);
+    }
+    // ADR V-cycle from zero on the joined levels l..LA, l > 2, prolonged into pinto.
+    void fuse_vcycle(int l, void* pinto) {
+        AdrLevel& A = c->al[l];
+        void* home[16];
+        for (int q = 2; q <= c->LA && q < 16; ++q) home[q] = c->al[q].x;
+        int h = 0;
+        with_edge(fuse_ft(l), [&](auto e) {
+            constexpr int FT = decltype(e)::value;
+            LAUNCH(c, (2 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny), (k_fuse_gram<T, FT>), dim3(fuse_ng(l)),
+                   dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   fuse_part(h));
+        });
+        fuse_down_up(l, h);
+        fuse_up<false>(l, fuse_ng(l), h, pinto);
+        fuse_homes(home);
+    }
+    void adr_steps_fuse(int M) {
+        WaveLevel& W = c->wl[2];
+        AdrLevel& A = c->al[2];
+        void* const u_home = W.u;
+        void* const b_home = A.b;
+        void* home[16];
+        for (int q = 2; q <= c->LA && q < 16; ++q) home[q] = c->al[q].x;
+        const double nn = NN2(A.nx, A.ny);
+        const int ng = fuse_ng(2);
+        int h = 0;
+        with_edge(fuse_ft(2), [&](auto e) {
+            constexpr int FT = decltype(e)::value;
+            LAUNCH(c, (5 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_start<T, FT>), dim3(ng), dim3(FuseCfg<FT>::START), st,
+                   A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, mod_args(nullptr, A.b), fuse_part(h));
+            for (int s = 0; s < M; ++s) {
+                fuse_down_up(2, h);
+                if (s + 1 < M) {
+                    const ModArgs<T> ma = mod_args(W.u == u_home ? W.ualt : u_home, A.b == b_home ? A.balt : b_home);
+                    LAUNCH(c, (9 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_step<T, true, FT>), dim3(ng),
+                           dim3(FuseCfg<FT>::STEP), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, fuse_part(1 - h));
+                    std::swap(W.u, W.ualt);
+                    std::swap(A.b, A.balt);
+                    h = 1 - h;
+                } else {
+                    const ModArgs<T> ma = mod_args(u_home, nullptr);
+                    LAUNCH(c, (6 * sizeof(C) + 2 * sizeof(T)) * nn, (k_fuse_step<T, false, FT>), dim3(ng),
+                           dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, (double*)nullptr);
+                    if (W.u != u_home) std::swap(W.u, W.ualt);
+                }
+            }
+        });
+        if (A.b != b_home) std::swap(A.b, A.balt);
+        fuse_homes(home);
+    }
+
     void adr_steps(int M) {
         WaveLevel& W = c->wl[2];
         AdrLevel& A = c->al[2];
         void* const u_home = W.u;
         void* const b_home = A.b;
         const bool fused = adr_fused();
+        if (fused && M > 0 && fuse_levels(2)) {
+            adr_steps_fuse(M);
+            return;
+        }
         for (int s = 0; s < M; ++s) {
             if (c->nsets > 1) use_set(c, s % c->nsets);
             if (s == 0 || !fused)
@@ -663,6 +789,10 @@ struct Engine {
         AdrLevel& A = c->al[l];
         const bool coarse = l == c->LA;
         const int m = coarse ? c->d.gmres_coarse_m : c->d.gmres_m;
+        if (pinto && l > 2 && epi == EPI_X && fuse_levels(l)) {
+            fuse_vcycle(l, pinto);
+            return;
+        }
         if (!coarse) {
             presmooth_restrict(l);
             adr_vcycle(l + 1, EPI_X, nullptr, A.x);
