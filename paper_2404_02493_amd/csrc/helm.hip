@@ -22,6 +22,7 @@
 #include "../../include/helm.h"
 #include "kernels_tail.hpp"
 #include "kernels_adrfuse.hpp"
+#include "kernels_chebm.hpp"
 #include "kernels_adjoint.hpp"
 #include "kernels_wtail.hpp"
 #include "kernels_eik.hpp"
@@ -473,6 +474,44 @@ struct Engine {
             prolong_add<T, T>(l, ec, u, assign);
     }
 
+    // ---- a level's Chebyshev smoothing and the transfer beside it in one pass each
+    bool cheb_passes() const { return c->d.cheb_pre <= CHEBM && c->d.cheb_post <= CHEBM; }
+    // f(tile edge) for level l: 16 while that is at most one block per CU, then 32, then 62 in
+    // FP32 (the largest whose buffers fit the LDS with whole wavefronts busy).
+    template <typename F>
+    void with_cheb_edge(int l, F&& f) const {
+        const int nx = c->wl[l].nx, ny = c->wl[l].ny;
+        if (fuse_tiles(nx, ny, 16) <= 256) return f(std::integral_constant<int, 16>{});
+        if constexpr (sizeof(T) == 4)
+            if (fuse_tiles(nx, ny, 32) > 256) return f(std::integral_constant<int, 62>{});
+        f(std::integral_constant<int, 32>{});
+    }
+    // u = Chebyshev(0, g_l), g_{l+1} = R (g_l - A u)
+    template <typename Tc>
+    void cheb_down(int l, void* u) {
+        WaveLevel& W = c->wl[l];
+        const int m = c->d.cheb_pre;
+        with_cheb_edge(l, [&](auto e) {
+            constexpr int FT = decltype(e)::value;
+            LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
+                   (k_cheb_down<T, Tc, FT>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (const T*)W.n2, (const C*)W.g, (C*)u, (cplx<Tc>*)c->wl[l + 1].g, cheb_table(l, m, c->w[l - 1]), m);
+        });
+    }
+    // u_l = Chebyshev(u + P u_{l+1}, g_l)
+    template <typename Tc>
+    void cheb_up(int l, const void* u) {
+        WaveLevel& W = c->wl[l];
+        const int m = c->d.cheb_post;
+        with_cheb_edge(l, [&](auto e) {
+            constexpr int FT = decltype(e)::value;
+            LAUNCH(c, (3 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
+                   (k_cheb_up<T, Tc, FT>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (const T*)W.n2, (const C*)W.g, (const C*)u, (const cplx<Tc>*)c->wl[l + 1].u, (C*)W.u,
+                   cheb_table(l, m, c->w[l - 1]), m);
+        });
+    }
+
     // ---- the coarsest wave level (always FP64)
     void coarsest(int l) {
         WaveLevel& W = c->wl[l];
@@ -516,6 +555,17 @@ struct Engine {
         }
         if (l == L) {
             coarsest(l);
+            return;
+        }
+        if (l != 3 && cheb_passes()) {
+            // the iterate waits in W.r while the coarser levels run
+            const bool c64 = c->wl[l + 1].f64;
+            if (c64) cheb_down<double>(l, W.r);
+            else cheb_down<T>(l, W.r);
+            cycle_coarse(l + 1);
+            if (c64) cheb_up<double>(l, W.r);
+            else cheb_up<T>(l, W.r);
+            if (l == 2 && c->d.adr_steps > 0 && L >= 3) adr_steps(c->d.adr_steps);
             return;
         }
         bool u_zero = true;
