@@ -7,7 +7,8 @@
 //                    units recompute fewer warm-up rows and leave fewer partials to
 //                    sum, shorter ones give more wavefronts), or 1 / 2 for the
 //                    overlapped-tile form with 16 x 16 / 32 x 32 tiles (more
-//                    parallelism on small levels, more recomputed ring nodes);
+//                    parallelism on small levels, more recomputed ring nodes); 0 on a level
+//                    and all below it joins them across their Gram passes where that applies;
 //   fgmres_blocks    blocks of the outer FGMRES passes on the fine grid.
 // Every candidate runs the real kernels on the level's buffers filled with
 // hashed data; the fastest (HIP-event time over a few repetitions) is kept.  The
@@ -106,10 +107,8 @@ static std::string tune_ctx(helm_ctx c, hipStream_t st) {
             HIPCHK(hipGetLastError());
             int best = 0;
             double tbest = 1e30;
-            for (int cand : {1, 2, 16, 24, 32, 40, 48, 64, 80, 96, 128}) {
-                if (cand > 16 && cand >= 2 * A.ny) break;  // segments run down the rows
-                c->tn.sstep_rows[l] = cand;
-                const double t = time_ms(st, reps, [&] {
+            auto timed = [&] {
+                return time_ms(st, reps, [&] {
                     if (l > 2) {
                         E.adr_vcycle(l, EPI_X, nullptr, c->al[l - 1].x);
                     } else if (c->phase_set) {
@@ -119,6 +118,11 @@ static std::string tune_ctx(helm_ctx c, hipStream_t st) {
                         E.gmres(l, m, false);
                     }
                 });
+            };
+            for (int cand : {1, 2, 16, 24, 32, 40, 48, 64, 80, 96, 128}) {
+                if (cand > 16 && cand >= 2 * A.ny) break;  // segments run down the rows
+                c->tn.sstep_rows[l] = cand;
+                const double t = timed();
                 note("sstep_l" + std::to_string(l) + "_" + (cand == 1 ? std::string("tile16") : cand == 2 ? std::string("tile32") : std::to_string(cand)), t);
                 if (t < tbest) {
                     tbest = t;
@@ -126,6 +130,18 @@ static std::string tune_ctx(helm_ctx c, hipStream_t st) {
                 }
             }
             c->tn.sstep_rows[l] = best;
+            // levels l..LA joined across their Gram passes (every one at its default form)
+            if (l > 2 || c->phase_set) {
+                const helm_ctx_s::Tuning chosen = c->tn;
+                for (int q = l; q <= c->LA && q < 16; ++q) c->tn.sstep_rows[q] = 0;
+                bool joined = E.fuse_levels(l);
+                if (joined) {
+                    const double t = timed();
+                    note("sstep_l" + std::to_string(l) + "_joined", t);
+                    joined = t < tbest;
+                }
+                if (!joined) c->tn = chosen;
+            }
         }
     }
     // outer FGMRES passes on the fine grid (basis of the inner solver for complex64
