@@ -47,18 +47,22 @@ __global__ __launch_bounds__(BLOCK) void k_eik_fill(size_t N, double v, double* 
     for (size_t p = blockIdx.x * (size_t)BLOCK + threadIdx.x; p < N; p += (size_t)gridDim.x * BLOCK) x[p] = v;
 }
 
-// One round (four passes); a pass is one launch per anti-diagonal d of the Ty x Tx tiles
-// (I + J = d, I < Ty rows, J < Tx columns).
+// One round: the passes (i up, j up) and (i up, j down), then the two with i down; a launch
+// takes one anti-diagonal of the Ty x Tx tiles of the first pass and the one Tx + 1 behind
+// it of the second.
 template <int B>
 static void eik_round(const EikSrc& E, const double* s, double* t1, double* part, hipStream_t st) {
-    const int Tx = E.nx / B, Ty = E.ny / B;
-    for (int pass = 0; pass < 4; ++pass) {
-        const int iup = pass < 2 ? 1 : 0, jup = (pass % 2) == 0 ? 1 : 0;
-        for (int d = 0; d <= Tx + Ty - 2; ++d) {
-            const int lo = std::max(0, d - Tx + 1), hi = std::min(d, Ty - 1);
-            hipLaunchKernelGGL((k_eik_pass<B>), dim3(hi - lo + 1), dim3(B), 0, st, E, s, t1, iup, jup, d, part);
+    const int Tx = E.nx / B, Ty = E.ny / B, last = Tx + Ty - 2;
+    auto tiles = [&](int d) { return d < 0 || d > last ? 0 : std::min(d, Ty - 1) - std::max(0, d - Tx + 1) + 1; };
+    for (int iup = 1; iup >= 0; --iup)
+        for (int d1 = 0; d1 <= last + Tx + 1; ++d1) {
+            const int d2 = d1 - (Tx + 1), n1 = tiles(d1), n2 = tiles(d2);
+            if (n1 + n2 == 0) continue;
+            if (iup)
+                hipLaunchKernelGGL((k_eik_pass<B, true>), dim3(n1 + n2), dim3(EIK_TB), 0, st, E, s, t1, d1, n1, d2, part);
+            else
+                hipLaunchKernelGGL((k_eik_pass<B, false>), dim3(n1 + n2), dim3(EIK_TB), 0, st, E, s, t1, d1, n1, d2, part);
         }
-    }
 }
 
 // Returns HELM_ENOCONV (phase unchanged) if a node is still unreached after max_rounds.
@@ -83,7 +87,8 @@ static helm_status eikonal(helm_ctx c, const double* src, int nsrc, int max_roun
     HIPCHK(hipMalloc((void**)&b.t1, NF * sizeof(double)));
     HIPCHK(hipMalloc((void**)&b.phi, NF * sizeof(double)));
     HIPCHK(hipMalloc((void**)&b.part, NT * sizeof(double)));
-    HIPCHK(hipMalloc((void**)&b.mx, 2 * sizeof(double)));
+    constexpr int MAXB = 256;  // blocks of the first stage of the maximum over the grid
+    HIPCHK(hipMalloc((void**)&b.mx, (1 + MAXB) * sizeof(double)));
     HIPCHK(hipHostMalloc((void**)&b.host, 2 * sizeof(double), hipHostMallocDefault));
     hipLaunchKernelGGL(k_eik_slowness, dim3(flat_blocks(NF)), dim3(BLOCK), 0, st, NF, (const double*)c->n2f, b.s);
     hipLaunchKernelGGL(k_eik_fill, dim3(flat_blocks(NF)), dim3(BLOCK), 0, st, NF, __builtin_huge_val(), b.phi);
@@ -113,7 +118,8 @@ static helm_status eikonal(helm_ctx c, const double* src, int nsrc, int max_roun
             if (tol >= 0.0 && last <= tol) break;
         }
         // a node still at +inf was never reached
-        hipLaunchKernelGGL(k_eik_max, dim3(1), dim3(1024), 0, st, NF, (const double*)b.t1, b.mx);
+        hipLaunchKernelGGL(k_eik_max, dim3(MAXB), dim3(1024), 0, st, NF, (const double*)b.t1, b.mx + 1);
+        hipLaunchKernelGGL(k_eik_max, dim3(1), dim3(1024), 0, st, (size_t)MAXB, (const double*)b.mx + 1, b.mx);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(b.host, b.mx, sizeof(double), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));

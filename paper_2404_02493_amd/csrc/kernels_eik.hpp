@@ -14,17 +14,20 @@
 // Fast sweeping: Gauss-Seidel passes in the four orders (i up, j up), (i up, j down),
 // (i down, j up), (i down, j down).  A pass runs as a wavefront over B x B tiles
 // (B = 64, or the shorter side when smaller; B divides both sides): the tiles of one
-// anti-diagonal (in the pass's orientation) are independent
-// and form one launch, one wavefront per tile; inside a tile the wavefront walks
-// the node anti-diagonals with the tile and its one-node halo in LDS.  A node then
-// sees exactly the values the sequential pass would give it (updated neighbours
+// anti-diagonal (in the pass's orientation) are independent, one block per tile; inside a
+// tile one wavefront walks the node anti-diagonals, lane l holding row l of the tile.  A
+// node then sees exactly the values the sequential pass would give it (updated neighbours
 // behind it, old ones ahead), so every pass equals the sequential one; the local
 // update rounds every operation separately (no contraction; quotients by h = 2^-m
 // are the exact products by 1/h), so the result is the same double precision numbers
 // as a sequential implementation of the same steps.
+// The two passes with the same direction of i run together, the second one Tx + 1 tile
+// diagonals behind the first: it then meets only tiles whose neighbours the first has
+// finished, and never a neighbour that the first still has to read (2 Tx + Ty launches for
+// the pair instead of 2 (Tx + Ty - 1)).
 #pragma once
 
-#include "kernels_adr.hpp"
+#include "kernels_sstep.hpp"
 
 namespace helm {
 
@@ -41,72 +44,30 @@ __device__ __forceinline__ double eik_r(const EikSrc& E, int i, int j) {
     return sqrt(dx * dx + dy * dy);
 }
 
-// New tau1 at global node (i, j) (not fixed, r = tau0 there, sp = s there) from the
-// neighbour values tw, te, ts, tn (+inf where missing or not reached yet) and their
-// tau0 values rw, re, rs, rn, or +inf when no candidate exists.  h = 1/max(nx, ny) is a
-// power of two, so a quotient by h is the product by max(nx, ny), exactly.
-__device__ __forceinline__ double eik_update(const EikSrc& E, int i, int j, double r, double sp, double tw,
-                                             double te, double ts, double tn, double rw, double re, double rs,
-                                             double rn) {
+// New tau1 at a node that is not fixed: rn = tau0 / h there, (gx, gy) = grad tau0, sp = s,
+// from the neighbour values tw, te, ts, tn (+inf where missing or not reached yet) and
+// their tau0 values rw, re, rs, rm (south, north); +inf when no candidate exists.  The sign
+// sgn = +-1 of the chosen neighbour is taken out of the axis's a and b (sgn a = rn + sgn g and
+// sgn b = rn t(q)): every product and quotient that they enter holds the sign twice or is
+// compared with its sign, and a change of sign rounds nothing.
+__device__ __forceinline__ double eik_update(double rn, double gx, double gy, double sp, double tw, double te,
+                                             double ts, double tn, double rw, double re, double rs, double rm) {
 #pragma clang fp contract(off)
     const double inf = __builtin_huge_val();
-    const double h = E.h, nh = double(E.nx > E.ny ? E.nx : E.ny);
-    const double dx = double(j) * h - E.xs, dy = double(i) * h - E.ys;
-    const double gx = dx / r, gy = dy / r;
-    bool hx = false, hy = false;
-    double tqx = inf, tqy = inf, ux = 0.0, uy = 0.0, sgx = 0.0, sgy = 0.0;
-    if (tw < inf) {
-        hx = true;
-        tqx = rw * tw;
-        ux = tw;
-        sgx = 1.0;
-    }
-    if (te < inf) {
-        const double v = re * te;
-        if (!hx || v < tqx) {
-            hx = true;
-            tqx = v;
-            ux = te;
-            sgx = -1.0;
-        }
-    }
-    if (ts < inf) {
-        hy = true;
-        tqy = rs * ts;
-        uy = ts;
-        sgy = 1.0;
-    }
-    if (tn < inf) {
-        const double v = rn * tn;
-        if (!hy || v < tqy) {
-            hy = true;
-            tqy = v;
-            uy = tn;
-            sgy = -1.0;
-        }
-    }
+    // a missing neighbour (+inf) is never the smaller one; of equal ones west and south
+    const bool east = re * te < rw * tw, north = rm * tn < rs * ts;
+    const double ux = east ? te : tw, uy = north ? tn : ts;
+    const double ax = east ? rn - gx : rn + gx, ay = north ? rn - gy : rn + gy;
+    const bool hx = ux < inf, hy = uy < inf;
+    const double bx = rn * ux, by = rn * uy;
+    const double A = ax * ax + ay * ay, B = ax * bx + ay * by, C = (bx * bx + by * by) - sp * sp;
+    const double disc = B * B - A * C;
+    const double t2 = (B + sqrt(disc)) / A;  // NaN or unused unless both axes have a neighbour
+    const double tx = (bx + sp) / ax, ty = (by + sp) / ay;
     double best = inf;
-    const double s2 = sp * sp;
-    const double ax = sgx * r * nh + gx, bx = sgx * r * ux * nh;
-    const double ay = sgy * r * nh + gy, by = sgy * r * uy * nh;
-    if (hx && hy) {
-        const double A = ax * ax + ay * ay, B = ax * bx + ay * by, C = (bx * bx + by * by) - s2;
-        if (A > 0.0) {
-            const double disc = B * B - A * C;
-            if (disc >= 0.0) {
-                const double t = (B + sqrt(disc)) / A;
-                if (sgx * (ax * t - bx) >= 0.0 && sgy * (ay * t - by) >= 0.0 && t < best) best = t;
-            }
-        }
-    }
-    if (hx && sgx * ax > 0.0) {
-        const double t = (bx + sgx * sp) / ax;
-        if (t < best) best = t;
-    }
-    if (hy && sgy * ay > 0.0) {
-        const double t = (by + sgy * sp) / ay;
-        if (t < best) best = t;
-    }
+    if (hx && hy && A > 0.0 && disc >= 0.0 && ax * t2 - bx >= 0.0 && ay * t2 - by >= 0.0 && t2 < best) best = t2;
+    if (hx && ax > 0.0 && tx < best) best = tx;
+    if (hy && ay > 0.0 && ty < best) best = ty;
     return best;
 }
 
@@ -129,80 +90,152 @@ __global__ __launch_bounds__(BLOCK) void k_eik_init(EikSrc E, const double* __re
     }
 }
 
-// One anti-diagonal d of B x B tiles of the pass (iup, jup): tile (I, J) of the
-// pass's orientation (a = iup ? i : ny-1-i, b = jup ? j : nx-1-j) with I + J = d; B
-// threads, B divides nx and ny.  part[tile] (tile in grid orientation, nx / B tiles per
-// row) keeps the largest single decrease of tau1 in the round.
+// One tile of the pass (IUP, JUP): tile (I, J) of the pass's orientation
+// (a = IUP ? i : ny-1-i, b = JUP ? j : nx-1-j); EIK_TB threads, B divides nx and ny.
+// part[tile] (tile in grid orientation, nx / B tiles per row) keeps the largest single
+// decrease of tau1 in the round.
+// Bound by the issue of the node chain: 2 B - 1 dependent updates of one wavefront.  So all
+// threads first stage tau1 and its geometry (tau0 and grad tau0, two divisions and a square
+// root a node) in LDS, and the chain keeps the neighbours behind a node in registers (its own
+// last value; the lane before it), reads everything ahead one step early and has no
+// barrier.  s is read from global memory PF steps early (with it the LDS would be full).
+constexpr int EIK_TB = 256;
 template <int B>
-__global__ __launch_bounds__(B) void k_eik_pass(EikSrc E, const double* __restrict__ s, double* __restrict__ t1,
-                                                int iup, int jup, int d, double* __restrict__ part) {
-    constexpr int R = B + 2;
-    __shared__ double tl[R * R];  // tau1 of the tile and its halo
-    __shared__ double rl[R * R];  // tau0 there
-    __shared__ double sl[B * B];
-    __shared__ double red[B];
+struct EikLds {
+    static constexpr int R = B + 2;
+    double tl[R * R + 8];  // tau1 of the tile and its halo (the margin is read, not used)
+    double rl[R * R + 8];  // tau0 there
+    double gx[B * B + B], gy[B * B + B];
+};
+template <int B, bool IUP, bool JUP>
+__device__ __forceinline__ void eik_tile(const EikSrc& E, const double* __restrict__ s, double* __restrict__ t1, int I,
+                                         int J, double* __restrict__ part, EikLds<B>& L) {
+    constexpr int R = EikLds<B>::R, PF = 8;
     const int n = E.nx, ny = E.ny, Tx = n / B, Ty = ny / B;
-    const int I = (d < Tx ? 0 : d - Tx + 1) + (int)blockIdx.x, J = d - I;
     const int a0 = I * B, b0 = J * B;
-    const int lane = threadIdx.x;
     const double inf = __builtin_huge_val();
-    auto gi = [&](int a) { return iup ? a : ny - 1 - a; };
-    auto gj = [&](int b) { return jup ? b : n - 1 - b; };
-    for (int q = lane; q < R * R; q += B) {
-        const int a = a0 - 1 + q / R, b = b0 - 1 + q % R;
+    auto gi = [&](int a) { return IUP ? a : ny - 1 - a; };
+    auto gj = [&](int b) { return JUP ? b : n - 1 - b; };
+    for (int q = threadIdx.x; q < R * R; q += EIK_TB) {
+        const int la = q / R - 1, lb = q % R - 1;
+        const int a = a0 + la, b = b0 + lb;
         const bool in = a >= 0 && a < ny && b >= 0 && b < n;
-        tl[q] = in ? t1[(size_t)gi(a) * n + gj(b)] : inf;
-        rl[q] = in ? eik_r(E, gi(a), gj(b)) : 0.0;
+        L.tl[q] = in ? t1[(size_t)gi(a) * n + gj(b)] : inf;
+        const double r = in ? eik_r(E, gi(a), gj(b)) : 1.0;  // off the grid: 1.0 * inf, never the smaller
+        L.rl[q] = r;
+        if (la >= 0 && la < B && lb >= 0 && lb < B) {
+#pragma clang fp contract(off)
+            L.gx[la * B + lb] = (double(gj(b)) * E.h - E.xs) / r;
+            L.gy[la * B + lb] = (double(gi(a)) * E.h - E.ys) / r;
+        }
     }
-    for (int q = lane; q < B * B; q += B) sl[q] = s[(size_t)gi(a0 + q / B) * n + gj(b0 + q % B)];
     __syncthreads();
-    // neighbours in grid orientation: west (j-1) is b-1 when jup, b+1 otherwise
-    const int dw = jup ? -1 : 1, ds = iup ? -1 : 1;
-    double dmax = 0.0;
-    for (int k = 0; k < 2 * B - 1; ++k) {
-        const int la = lane, lb = k - lane;
-        if (lb >= 0 && lb < B) {
-            const int i = gi(a0 + la), j = gj(b0 + lb);
-            const int q = (la + 1) * R + (lb + 1);
-            const double r = rl[q];
-            if (r > E.rfix) {
-                const double t = eik_update(E, i, j, r, sl[la * B + lb], tl[q + dw], tl[q - dw], tl[q + ds * R],
-                                            tl[q - ds * R], rl[q + dw], rl[q - dw], rl[q + ds * R], rl[q - ds * R]);
-                const double old = tl[q];
-                if (t < old) {
-                    const double dec = old == inf ? inf : old - t;
+    if (threadIdx.x < 64) {
+        const double nh = double(n > ny ? n : ny);
+        const int la = threadIdx.x < B ? (int)threadIdx.x : B - 1;
+        const bool row = threadIdx.x < B;
+        // at step k this lane is at column k - la; LDS positions of column 0 of its row
+        double* tl = L.tl + (la + 1) * R + 1 - la;
+        const double* rl = L.rl + (la + 1) * R + 1 - la;
+        const double* gxl = L.gx + la * B - la;
+        const double* gyl = L.gy + la * B - la;
+        const double* srow = s + (size_t)gi(a0 + la) * n;
+        auto s_at = [&](int k) {  // s at step k (any column of the row where the lane is not in the tile)
+            const int lb = k - la;
+            return srow[gj(b0 + (lb < 0 ? 0 : lb >= B ? B - 1 : lb))];
+        };
+        double sv[PF];
+#pragma unroll
+        for (int q = 0; q < PF; ++q) sv[q] = s_at(q);
+        double tp = tl[-1], tc = tl[0], tx = tl[1];  // tau1 behind (updated), at and ahead of the node
+        double rp = rl[-1], rc = rl[0], rx = rl[1];
+        double tb = tl[-R], ta = tl[R], rb = rl[-R], ra = rl[R], gx = gxl[0], gy = gyl[0];
+        double dmax = 0.0;
+        // 2 B - 1 steps, rounded up to PF (no lane is in the tile in the last one)
+        for (int k0 = 0; k0 < 2 * B; k0 += PF) {
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                const int k = k0 + q;
+                // everything ahead of the next node, none of it written before the next step
+                const double txn = tl[k + 2], tbn = tl[k + 1 - R], tan = tl[k + 1 + R];
+                const double rxn = rl[k + 2], rbn = rl[k + 1 - R], ran = rl[k + 1 + R];
+                const double gxn = gxl[k + 1], gyn = gyl[k + 1];
+                const double sp = sv[q];
+                sv[q] = s_at(k + PF);
+                // behind in the other axis: the last value of the lane before (row -1: the halo)
+                const double tprev = lane_prev(tp);
+                const double tbr = la == 0 ? tb : tprev;
+                const double t = eik_update(rc * nh, gx, gy, sp, JUP ? tp : tx, JUP ? tx : tp, IUP ? tbr : ta,
+                                            IUP ? ta : tbr, JUP ? rp : rx, JUP ? rx : rp, IUP ? rb : ra,
+                                            IUP ? ra : rb);
+                const int lb = k - la;
+                const bool on = row && lb >= 0 && lb < B;
+                if (on && rc > E.rfix && t < tc) {
+                    const double dec = tc - t;  // +inf for a node not reached before
                     dmax = dec > dmax ? dec : dmax;
-                    tl[q] = t;
+                    tl[k] = t;
+                    tc = t;
                 }
+                tp = tc;  // off the tile: what lies to the left of the next node
+                tc = tx;
+                tx = txn;
+                rp = rc;
+                rc = rx;
+                rx = rxn;
+                tb = tbn;
+                ta = tan;
+                rb = rbn;
+                ra = ran;
+                gx = gxn;
+                gy = gyn;
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double o = __shfl_xor(dmax, off, 64);
+            dmax = o > dmax ? o : dmax;
+        }
+        if (threadIdx.x == 0) {
+            const int ti = IUP ? I : Ty - 1 - I, tj = JUP ? J : Tx - 1 - J;
+            double* pp = part + (size_t)ti * Tx + tj;
+            *pp = dmax > *pp ? dmax : *pp;
+        }
     }
-    for (int q = lane; q < B * B; q += B) t1[(size_t)gi(a0 + q / B) * n + gj(b0 + q % B)] = tl[(q / B + 1) * R + q % B + 1];
-    red[lane] = dmax;
     __syncthreads();
-    if (lane == 0) {
-        double m = 0.0;
-        for (int q = 0; q < B; ++q) m = red[q] > m ? red[q] : m;
-        const int ti = iup ? I : Ty - 1 - I, tj = jup ? J : Tx - 1 - J;
-        double* pp = part + (size_t)ti * Tx + tj;
-        *pp = m > *pp ? m : *pp;
-    }
+    for (int q = threadIdx.x; q < B * B; q += EIK_TB)
+        t1[(size_t)gi(a0 + q / B) * n + gj(b0 + q % B)] = L.tl[(q / B + 1) * R + q % B + 1];
 }
 
-// out[0] = max of x[0..N) and of 0 (one block of 1024 threads; maxima are exact in
-// any order).
+// Anti-diagonal d1 of the pass (IUP, j up) in the first n1 blocks, d2 of the pass
+// (IUP, j down) in the others.
+template <int B, bool IUP>
+__global__ __launch_bounds__(EIK_TB) void k_eik_pass(EikSrc E, const double* __restrict__ s, double* __restrict__ t1,
+                                                     int d1, int n1, int d2, double* __restrict__ part) {
+    __shared__ EikLds<B> L;
+    const int Tx = E.nx / B;
+    const bool first = (int)blockIdx.x < n1;
+    const int d = first ? d1 : d2, x = first ? (int)blockIdx.x : (int)blockIdx.x - n1;
+    const int I = (d < Tx ? 0 : d - Tx + 1) + x;
+    if (first)
+        eik_tile<B, IUP, true>(E, s, t1, I, d - I, part, L);
+    else
+        eik_tile<B, IUP, false>(E, s, t1, I, d - I, part, L);
+}
+
+// out[block] = max of the block's share of x[0..N) and of 0 (blocks of 1024 threads; maxima
+// are exact in any order).
 __global__ __launch_bounds__(1024) void k_eik_max(size_t N, const double* __restrict__ x, double* __restrict__ out) {
     __shared__ double sm[1024];
     double m = 0.0;
-    for (size_t p = threadIdx.x; p < N; p += 1024) m = x[p] > m ? x[p] : m;
+    for (size_t p = (size_t)blockIdx.x * 1024 + threadIdx.x; p < N; p += (size_t)gridDim.x * 1024)
+        m = x[p] > m ? x[p] : m;
     sm[threadIdx.x] = m;
     __syncthreads();
     for (int w = 512; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) sm[threadIdx.x] = sm[threadIdx.x + w] > sm[threadIdx.x] ? sm[threadIdx.x + w] : sm[threadIdx.x];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = sm[0];
+    if (threadIdx.x == 0) out[blockIdx.x] = sm[0];
 }
 
 // phi = min(phi, tau0 tau1) (first arrival over the sources).
