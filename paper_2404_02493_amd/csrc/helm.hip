@@ -475,6 +475,9 @@ struct Engine {
     }
 
     // ---- a level's Chebyshev smoothing and the transfer beside it in one pass each
+    // (arithmetic type by tile edge: kernels_chebm.hpp)
+    template <int FT>
+    using ChebType = std::conditional_t<FT <= 32, double, T>;
     bool cheb_passes() const { return c->d.cheb_pre <= CHEBM && c->d.cheb_post <= CHEBM; }
     // f(tile edge) for level l: 16 while that is at most one block per CU, then 32, then 62 in
     // FP32 (the largest whose buffers fit the LDS with whole wavefronts busy).
@@ -494,7 +497,7 @@ struct Engine {
         with_cheb_edge(l, [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
-                   (k_cheb_down<T, Tc, FT>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (k_cheb_down<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
                    (const T*)W.n2, (const C*)W.g, (C*)u, (cplx<Tc>*)c->wl[l + 1].g, cheb_table(l, m, c->w[l - 1]), m);
         });
     }
@@ -506,7 +509,7 @@ struct Engine {
         with_cheb_edge(l, [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (3 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
-                   (k_cheb_up<T, Tc, FT>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (k_cheb_up<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
                    (const T*)W.n2, (const C*)W.g, (const C*)u, (const cplx<Tc>*)c->wl[l + 1].u, (C*)W.u,
                    cheb_table(l, m, c->w[l - 1]), m);
         });

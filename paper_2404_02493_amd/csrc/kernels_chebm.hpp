@@ -23,7 +23,7 @@ struct ChebCfg {
     static constexpr int FB = FT == 16 ? 704 : FT == 32 ? 704 : 1024;
 };
 
-// A region of RW x RW nodes of a wave level from node (i0, j0), thread t owning the nodes
+// A region of RW x RW nodes (arithmetic type T) of a wave level from node (i0, j0), thread t owning the nodes
 // t, t + FB, ...
 template <typename T, int RW, int FB>
 struct ChebReg {
@@ -50,10 +50,15 @@ struct ChebReg {
             p[k] = ok[k] ? (unsigned)(gi * G.nx + gj) : 0u;
         }
     }
-    template <typename V>
-    __device__ __forceinline__ void load(const V* __restrict__ a, V (&v)[NPT]) const {
+    template <typename S>
+    __device__ __forceinline__ void load(const cplx<S>* __restrict__ a, cplx<T> (&v)[NPT]) const {
 #pragma unroll
-        for (int k = 0; k < NPT; ++k) v[k] = ld_off(a, p[k]);
+        for (int k = 0; k < NPT; ++k) v[k] = ccast<T>(ld_off(a, p[k]));
+    }
+    template <typename S>
+    __device__ __forceinline__ void load(const S* __restrict__ a, T (&v)[NPT]) const {
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) v[k] = T(ld_off(a, p[k]));
     }
     __device__ __forceinline__ void coefs(const Geom& G, const T (&n2)[NPT], int i0, int j0) {
         const T ih2 = T(G.inv_h2);
@@ -111,10 +116,10 @@ struct ChebReg {
 
 // u = m Chebyshev steps from 0 for A u = g (every node of u written, 0 on the ring) and
 // rc = R (g - A u) on the coarse grid; fuse_tiles(G.nx, G.ny, FT) blocks, m <= CHEBM.
-template <typename T, typename Tc, int FT>
-__global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_down(Geom G, const T* __restrict__ n2,
-                                                               const cplx<T>* __restrict__ g,
-                                                               cplx<T>* __restrict__ uout, cplx<Tc>* __restrict__ rc,
+template <typename S, typename Tc, int FT, typename T>
+__global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_down(Geom G, const S* __restrict__ n2,
+                                                               const cplx<S>* __restrict__ g,
+                                                               cplx<S>* __restrict__ uout, cplx<Tc>* __restrict__ rc,
                                                                const double* __restrict__ cc, int m, BatchIdx bi) {
     bshift(bi.off(), n2, g, uout, rc, cc);
     // u is needed one node before the tile and two behind it (the residual on the tile and one
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_down(Geom G, const T* 
     F.load(g, gv);
 #pragma unroll
     for (int k = 0; k < R::NPT; ++k)
-        if (R::in(k, LO, LO + FT - 1) && F.ok[k]) st_off(uout, F.p[k], u[k]);
+        if (R::in(k, LO, LO + FT - 1) && F.ok[k]) st_off(uout, F.p[k], ccast<S>(u[k]));
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < R::NPT; ++k) s1[R::S0 + R::q(k)] = gv[k] - F.template apply<false>(s0, k);
@@ -172,11 +177,11 @@ __global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_down(Geom G, const T* 
 
 // uout = m Chebyshev steps from u_in + P ec for A u = g (every node written, 0 on the ring);
 // fuse_tiles(G.nx, G.ny, FT) blocks, m <= CHEBM; uout must not overlap uin.
-template <typename T, typename Tc, int FT>
-__global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_up(Geom G, const T* __restrict__ n2,
-                                                             const cplx<T>* __restrict__ g,
-                                                             const cplx<T>* __restrict__ uin,
-                                                             const cplx<Tc>* __restrict__ ec, cplx<T>* __restrict__ uout,
+template <typename S, typename Tc, int FT, typename T>
+__global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_up(Geom G, const S* __restrict__ n2,
+                                                             const cplx<S>* __restrict__ g,
+                                                             const cplx<S>* __restrict__ uin,
+                                                             const cplx<Tc>* __restrict__ ec, cplx<S>* __restrict__ uout,
                                                              const double* __restrict__ cc, int m, BatchIdx bi) {
     bshift(bi.off(), n2, g, uin, ec, uout, cc);
     constexpr int LO = 2 * CHEBM, RW = FT + 2 * LO, FB = ChebCfg<FT>::FB;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(ChebCfg<FT>::FB) void k_cheb_up(Geom G, const T* __
     F.steps(cc, m, u, r, s0, s1);
 #pragma unroll
     for (int k = 0; k < R::NPT; ++k)
-        if (R::in(k, LO, LO + FT - 1) && F.ok[k]) st_off(uout, F.p[k], u[k]);
+        if (R::in(k, LO, LO + FT - 1) && F.ok[k]) st_off(uout, F.p[k], ccast<S>(u[k]));
 }
 
 }  // namespace helm
