@@ -87,8 +87,9 @@ typedef struct {
                                  4096 nodes) runs its GMRES in one workgroup (default 64; 0 = never).  Not
                                  used where the ADR levels are joined across their Gram passes: GMRES(3)
                                  in s-step form on every level, no tuned form, small grids */
-    int32_t wave_tail_n;      /* the wave levels >= 3 with at most wave_tail_n nodes on the longer side run in
-                                 one workgroup, all of them in a single launch (default 32; 0 = never) */
+    int32_t wave_tail_n;      /* the wave levels >= 3 with at most wave_tail_n nodes on the longer side (and at
+                                 most 4096 nodes) run in one workgroup, all of them in a single launch
+                                 (default 32; 0 = never); an unsmoothed level 3 joins those below it */
     double shift;             /* relative imaginary shift s0 >= 0 of the shifted equation (Section 4.3.2,
                                  gamma_0 = s0 k(x)^2 with k(x) = k n(x); the paper's test uses 0.01):
                                  kappa = k^2 n^2 (1 + i sigma (delta + s0)); default 0 */

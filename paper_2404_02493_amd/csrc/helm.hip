@@ -532,9 +532,6 @@ struct Engine {
             t.n2 = W.n2;
             t.g = W.g;
             t.u = W.u;
-            t.r = W.r;
-            t.d = W.d;
-            t.t = W.t;
             t.la = c->cdev->la + 2 * l;
         }
         a.l0 = l0;
@@ -543,9 +540,12 @@ struct Engine {
         a.cheb_post = c->d.cheb_post;
         a.cheb_coarse = c->d.cheb_coarse;
         a.level3_literal = c->d.level3_literal;
-        double bytes = 0.0;
-        for (int l = l0; l <= c->L; ++l) bytes += 8.0 * csize(c->wl[l].f64) * NN2(c->wl[l].nx, c->wl[l].ny);
-        LAUNCH(c, bytes, (k_wave_tail<T>), dim3(1), dim3(WT_THREADS), st, a);
+        const WaveLevel& W0 = c->wl[l0];
+        const double bytes = 2.0 * csize(W0.f64) * NN2(W0.nx, W0.ny);
+        if ((size_t)W0.nx * W0.ny <= WT_THREADS)
+            LAUNCH(c, bytes, (k_wave_tail<1>), dim3(1), dim3(WT_THREADS), st, a);
+        else
+            LAUNCH(c, bytes, (k_wave_tail<4>), dim3(1), dim3(WT_THREADS), st, a);
     }
 
     // ---- one cycle on level l >= 2 with zero initial iterate: u_l from g_l
@@ -1390,13 +1390,19 @@ static void build(helm_ctx c, const double* velocity, hipStream_t st) {
             HIPCHK(hipFree(tmp));
         }
     }
-    // first level (>= 3) small enough for the one-workgroup tail of the wave cycle
+    // first level (>= 3) small enough for the one-workgroup tail of the wave cycle; level 3
+    // without smoothing (two transfers) joins a tail that would begin at level 4
     c->LT = 0;
-    for (int l = 3; l <= L && l <= WT_MAXL; ++l)
-        if (std::max(c->wl[l].nx, c->wl[l].ny) <= d.wave_tail_n) {
+    auto wt_fits = [&](int l) {
+        const WaveLevel& W = c->wl[l];
+        return (size_t)W.nx * W.ny <= WT_NODES && std::max(W.nx, W.ny) <= WT_ROW;
+    };
+    for (int l = 3; l <= L && L <= WT_MAXL; ++l)
+        if (std::max(c->wl[l].nx, c->wl[l].ny) <= d.wave_tail_n && wt_fits(l)) {
             c->LT = l;
             break;
         }
+    if (c->LT == 4 && !d.level3_literal && wt_fits(3)) c->LT = 3;
     // default weights
     c->w.assign(L, 0.0);
     {

@@ -1,0 +1,49 @@
+"""GPU parity of the one-pass Chebyshev smoothings and of the one-workgroup wave tail
+against the FP64 oracle, through the cycle from level 2 and the fine cycle.
+
+Grids: levels smaller than a 16 x 16 tile, of a few, of 32 x 32 and (FP32) 62 x 62 tiles with
+remainders in both directions; step counts 1, 2, 5 and 6 (the last beyond one pass);
+Algorithm 1's literal level 3; the tail off, from 32 nodes a side and from 64 (several nodes a
+thread), on squares and rectangles.  Tolerances as in the other parity tests: 1e-12 (FP64
+cycles) and 1e-5 (FP32 cycles), relative 2-norm and element by element.
+"""
+import numpy as np
+import pytest
+import torch
+
+import helm_inputs as hi
+from gpu_util import TOL, assert_close, rand_grid, rounded, to_dev
+from oracle.cycle import Problem, cycle, wave_adr_cycle
+
+pytestmark = pytest.mark.gpu
+
+# (rows, columns, levels, options of both sides, wave_tail_n)
+CASES = [(16, 16, 3, {}, 32), (32, 32, 4, {}, 0), (64, 64, 5, {}, 32), (128, 128, 6, {}, 32), (128, 128, 6, {}, 64),
+         (128, 128, 6, {"level3_literal": 1}, 64), (256, 256, 7, {}, 0), (256, 256, 7, {}, 32), (32, 512, 4, {}, 32),
+         (512, 32, 4, {}, 64), (64, 1024, 5, {}, 64), (128, 128, 5, {"cheb_pre": 1, "cheb_post": 2}, 32),
+         (128, 128, 5, {"cheb_pre": 6, "cheb_post": 5}, 32), (128, 128, 4, {"cheb_pre": 4, "cheb_coarse": 3}, 32),
+         (1024, 512, 6, {}, 32), (1024, 2048, 6, {}, 32)]
+
+
+@pytest.mark.parametrize("ny,nx,levels,opts,tail", CASES)
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_smoothers_and_tail(ny, nx, levels, opts, tail, prec):
+    from paper_2404_02493_amd import Helmholtz
+
+    c = hi.make_problem(nx, 0.5 * max(nx, ny), levels, seed=3 + nx + ny, medium="grf", phase="fmm",
+                        damping_cells=8 if min(nx, ny) > 16 else 2, ny=ny)
+    P = Problem(c.velocity, c.k, levels, damping_cells=c.damping_cells, phi=c.phi, adr_steps=1, **opts)
+    H = Helmholtz(c.velocity, c.k, levels=levels, precision=prec, damping_cells=c.damping_cells, adr_steps=1,
+                  wave_tail_n=tail, **opts)
+    H.set_phase(c.phi)
+    H.set_weights(P.weights.numpy())
+    cd = H.cdtype
+    rng = np.random.default_rng(nx + 7 * ny)
+    g2 = rounded(rand_grid(rng, (ny // 2, nx // 2)), cd)
+    out = H.debug_op(10, 2, None, to_dev(g2, cd))
+    assert_close(out, wave_adr_cycle(P, 2, g2, torch.zeros_like(g2)), TOL[prec], "cycle from level 2")
+    u, g = rounded(rand_grid(rng, (ny, nx)), cd), rounded(torch.as_tensor(c.g), cd)
+    ud = to_dev(u, cd)
+    H.cycle(to_dev(g, cd), ud)
+    assert_close(ud, cycle(P, g, u), TOL[prec], "cycle")
+    H.close()
