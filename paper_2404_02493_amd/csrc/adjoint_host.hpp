@@ -432,13 +432,13 @@ struct AdjEngine {
         const size_t NF = N(1);
         const int nb = fb(NF);
         LAUNCH_NB(c, (5.0 * sizeof(C) + sizeof(T)) * NF, (k_jacobi_adj<T>), dim3(nb), dim3(BLOCK), st, G, (const T*)W.n2,
-               (const C*)g, (const C*)tp().uB, (const C*)S.fb[0], (C*)S.fb[1], T(c->w[0]), wslot());
+               (const C*)g, (const C*)tp().uB, (const C*)S.fb[0], (C*)S.fb[1], (const double*)c->cdev->la, wslot());
         fin_add(nb, 0);
         restrict_adj(1, S.fb[1], S.lub[2]);
         rev_level(2);
         prolong_adj(1, S.lgb[2], S.fb[1], nullptr);
         LAUNCH_NB(c, ((u0 ? 5.0 : 4.0) * sizeof(C) + sizeof(T)) * NF, (k_jacobi_adj<T>), dim3(nb), dim3(BLOCK), st, G,
-               (const T*)W.n2, (const C*)g, (const C*)u0, (const C*)S.fb[1], (C*)S.fb[0], T(c->w[0]), wslot());
+               (const T*)W.n2, (const C*)g, (const C*)u0, (const C*)S.fb[1], (C*)S.fb[0], (const double*)c->cdev->la, wslot());
         fin_add(nb, 0);
         wflush();
     }
@@ -486,27 +486,15 @@ struct AdjEngine {
         auto& B = S.cs[l];
         Cp *r = (Cp*)B[0], *rt = (Cp*)B[1], *d = (Cp*)B[2], *dt = (Cp*)B[3], *s = (Cp*)B[4], *stt = (Cp*)B[5];
         Cp *t1 = (Cp*)B[6], *t2 = (Cp*)B[7], *res = (Cp*)B[8];
-        const double lam = W.lam;
-        const double a = lam / alpha;
-        const double th = 0.5 * (lam + a), dc = 0.5 * (lam - a);
-        const double th_t = -lam / (2.0 * alpha * alpha), dc_t = lam / (2.0 * alpha * alpha);
-        double rho = dc / th, rho_t = (dc_t * th - dc * th_t) / (th * th);
+        const double* tab = c->cdev->lv[l].adj[E.cheb_kind(l, m, alpha)];
         LAUNCH_NB(c, 7.0 * sizeof(Cp) * n, (k_chebadj_start<P>), dim3(nb), dim3(BLOCK), st, n, (const Cp*)ubar, r, rt, d,
-               dt, s, stt, P(1.0 / th), P(-th_t / (th * th)));
+               dt, s, stt, tab);
         // one fused pass per step; d, dt alternate with the buffers t1, t2
         for (int t = 1; t < m; ++t) {
-            const double den = 2.0 * th - dc * rho;
-            const double den_t = 2.0 * th_t - dc_t * rho - dc * rho_t;
-            const double rn = dc / den, rn_t = (dc_t * den - dc * den_t) / (den * den);
-            const double c1 = rn * rho, c1t = rn_t * rho + rn * rho_t;
-            const double c2 = 2.0 / den, c2t = -2.0 * den_t / (den * den);
             LAUNCH_NB(c, (14.0 * sizeof(Cp) + sizeof(P)) * n, (k_chebadj_fused<P>), dim3(tiles_of(G.nx, G.ny)),
-                      tile_block(), st, G, (const P*)W.n2, (const Cp*)d, (const Cp*)dt, t1, t2, r, rt, s, stt, P(c1),
-                      P(c2), P(c1t), P(c2t));
+                      tile_block(), st, G, (const P*)W.n2, (const Cp*)d, (const Cp*)dt, t1, t2, r, rt, s, stt, tab + 4 * t);
             std::swap(d, t1);
             std::swap(dt, t2);
-            rho = rn;
-            rho_t = rn_t;
         }
         E.template residual<P>(G, W.n2, g, u, res);
         LAUNCH_NB(c, (2.0 * sizeof(Cp) + sizeof(P)) * n, (k_dot_ah<P>), dim3(nb), dim3(BLOCK), st, G, (const P*)W.n2,

@@ -135,8 +135,7 @@ static helm_status eikonal(helm_ctx c, const double* src, int nsrc, int max_roun
         change_max = std::max(change_max, last);
     }
     if (c->L >= 3) {
-        use_set(c, 0);
-        c->nsets = 1;
+        single_phase(c);
         if (nsrc == 1)
             build_phase_factored(c, b.t1, src[0], src[1], st);
         else
@@ -145,7 +144,6 @@ static helm_status eikonal(helm_ctx c, const double* src, int nsrc, int max_roun
     if (tau1_out) HIPCHK(hipMemcpyAsync(tau1_out, b.t1, NF * sizeof(double), hipMemcpyDeviceToDevice, st));
     if (phi_out) HIPCHK(hipMemcpyAsync(phi_out, b.phi, NF * sizeof(double), hipMemcpyDeviceToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
-    drop_graphs(c);
     c->phase_set = true;
     c->phase_factored = nsrc == 1 && c->L >= 3;
     ++c->data_gen;

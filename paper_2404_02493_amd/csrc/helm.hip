@@ -91,12 +91,18 @@ enum { ADJ_FULL = 0, ADJ_REC = 1, ADJ_REV = 2 };  // slots: record + reverse, re
 
 // Chebyshev coefficient tables and per-level (lambda, alpha) in device memory (one copy per
 // problem): la[0] = the Jacobi weight of level 1, la[2 l], la[2 l + 1] = (lambda_l, alpha_l);
-// cheb[l][kind] rows of 3 doubles, row 0 = {1/theta, 0, 0},
+// lv[l].cheb[kind] rows of 3 doubles, row 0 = {1/theta, 0, 0},
 // row s = {0, c1, c2} of step s; kind 0/1/2 = the pre, post and coarsest step counts.
+// lv[l].adj[kind] rows of 4 doubles for the reverse with the alpha tangents (' = d/d alpha):
+// row 0 = {1/theta, (1/theta)', 0, 0}, row s = {c1, c2, c1', c2'}.
+// Kernels read the weights here and nowhere else, so captured graphs outlive a change of them.
 constexpr int CHEB_ROWS = 65;
 struct CycleDev {
     double la[2 * 16];
-    double cheb[16][3][CHEB_ROWS * 3];
+    struct Level {
+        double cheb[3][CHEB_ROWS * 3];
+        double adj[3][CHEB_ROWS * 4];
+    } lv[16];
 };
 
 }  // namespace helm
@@ -404,12 +410,13 @@ struct Engine {
 
     // Coefficient table of level l for m steps (see CycleDev; the pre, post and coarsest
     // counts of the descriptor).
-    const double* cheb_table(int l, int m, double alpha) const {
+    int cheb_kind(int l, int m, double alpha) const {
         const int kind = m == c->d.cheb_pre ? 0 : m == c->d.cheb_post ? 1 : m == c->d.cheb_coarse ? 2 : -1;
         REQUIRE(kind >= 0, "Chebyshev step count without a coefficient table");
         REQUIRE(alpha == c->w[l - 1], "Chebyshev alpha other than the level's weight");
-        return c->cdev->cheb[l][kind];
+        return kind;
     }
+    const double* cheb_table(int l, int m, double alpha) const { return c->cdev->lv[l].cheb[cheb_kind(l, m, alpha)]; }
 
     template <typename P>
     void chebyshev(int l, const void* g, void* u, bool u_zero, double alpha, int m) {
@@ -1255,8 +1262,9 @@ static void write_cycle_tables(helm_ctx c) {
         const double a = lam / alpha;
         const double theta = 0.5 * (lam + a);
         const double dc = 0.5 * (lam - a);
+        const double th_t = -lam / (2.0 * alpha * alpha), dc_t = lam / (2.0 * alpha * alpha);
         for (int kind = 0; kind < 3; ++kind) {
-            double* t = h.cheb[l][kind];
+            double* t = h.lv[l].cheb[kind];
             t[0] = double(1.0 / theta);
             double rho = dc / theta;
             for (int step = 1; step < ms[kind] && step < CHEB_ROWS; ++step) {
@@ -1266,9 +1274,25 @@ static void write_cycle_tables(helm_ctx c) {
                 t[3 * step + 2] = 2.0 / den;
                 rho = rho_new;
             }
+            double* q = h.lv[l].adj[kind];
+            rho = dc / theta;
+            double rho_t = (dc_t * theta - dc * th_t) / (theta * theta);
+            q[0] = 1.0 / theta;
+            q[1] = -th_t / (theta * theta);
+            for (int step = 1; step < ms[kind] && step < CHEB_ROWS; ++step) {
+                const double den = 2.0 * theta - dc * rho;
+                const double den_t = 2.0 * th_t - dc_t * rho - dc * rho_t;
+                const double rn = dc / den, rn_t = (dc_t * den - dc * den_t) / (den * den);
+                q[4 * step] = rn * rho;
+                q[4 * step + 1] = 2.0 / den;
+                q[4 * step + 2] = rn_t * rho + rn * rho_t;
+                q[4 * step + 3] = -2.0 * den_t / (den * den);
+                rho = rn;
+                rho_t = rn_t;
+            }
         }
     }
-    HIPCHK(hipMemcpy(c->cdev, &h, sizeof(h), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(c->cdev, &h, offsetof(CycleDev, lv) + (c->L + 1) * sizeof(CycleDev::Level), hipMemcpyHostToDevice));
 }
 
 // ------------------------------------------------------------------ setup
@@ -1502,17 +1526,23 @@ static void build_phase(helm_ctx c, const void* phi, int is64, hipStream_t st) {
     HIPCHK(hipGetLastError());
 }
 
+// Back to one phase, set 0.  Captured graphs read the phase from its arrays, so they stay
+// valid when only the contents change; they hold other arrays after helm_set_rays.
+static void single_phase(helm_ctx c) {
+    use_set(c, 0);
+    if (c->nsets != 1) drop_graphs(c);
+    c->nsets = 1;
+}
+
 static void set_phase(helm_ctx c, const void* phi, int is64, hipStream_t st) {
     if (c->L < 3) {
         c->phase_set = true;
         ++c->data_gen;
         return;
     }
-    use_set(c, 0);
-    c->nsets = 1;
+    single_phase(c);
     build_phase(c, phi, is64, st);
     HIPCHK(hipStreamSynchronize(st));
-    drop_graphs(c);
     c->phase_set = true;
     c->phase_factored = false;
     ++c->data_gen;
@@ -1593,8 +1623,8 @@ static void drop_graphs(helm_ctx c) {
 
 // One cycle: replays the graph captured for these pointers (capturing it on first
 // use), or launches eagerly when graphs are off or per-launch profiling is on.
-// The cycle's kernel arguments depend only on the pointers and the weights, so a
-// graph stays valid until the weights change (drop_graphs).
+// The cycle's kernel arguments depend only on the pointers (phase and weights are read
+// from device memory), so a graph stays valid while the phase sets and the tuning do.
 static void cycle_any(helm_ctx c, const void* g, const void* u_in, void* u_out, hipStream_t st) {
     if (!c->d.use_graphs || c->prof.on) {
         cycle_eager(c, g, u_in, u_out, st);
@@ -1911,8 +1941,7 @@ helm_status helm_set_weights(helm_ctx ctx, const double* w) {
             if (l >= 1) REQUIRE(w[l] >= 1.0, "Chebyshev alpha must be >= 1");
         }
         ctx->w.assign(w, w + ctx->L);
-        write_cycle_tables(ctx);
-        drop_graphs(ctx);
+        write_cycle_tables(ctx);  // captured graphs read the weights from there
         ++ctx->data_gen;
         return HELM_OK;
     })

@@ -104,7 +104,9 @@ __global__ __launch_bounds__(FBLOCK) void k_wsum(const double* __restrict__ wpar
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_jacobi_adj(Geom G, const T* __restrict__ n2, const cplx<T>* __restrict__ g,
                                                       const cplx<T>* __restrict__ u, const cplx<T>* __restrict__ yb,
-                                                      cplx<T>* __restrict__ ub, T w, double* partials) {
+                                                      cplx<T>* __restrict__ ub, const double* __restrict__ wp,
+                                                      double* partials) {
+    const T w = T(wp[0]);
     const int n = G.nx;  // nodes per row
     const size_t N = (size_t)n * G.ny;
     double acc[1] = {0.0};
@@ -233,12 +235,13 @@ __global__ __launch_bounds__(BLOCK) void k_adj_ahsub(Geom G, const T* __restrict
 }
 
 // Chebyshev reverse, start of the primal + alpha-tangent recurrences on v:
-//   r = v, rt = 0, d = v / theta, dt = v * dt0, s = d, st = dt.
+//   r = v, rt = 0, d = v / theta, dt = v * dt0, s = d, st = dt   (cc = {1 / theta, dt0}).
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_chebadj_start(size_t N, const cplx<T>* __restrict__ v, cplx<T>* __restrict__ r,
                                                          cplx<T>* __restrict__ rt, cplx<T>* __restrict__ d,
                                                          cplx<T>* __restrict__ dt, cplx<T>* __restrict__ s,
-                                                         cplx<T>* __restrict__ st, T inv_theta, T dt0) {
+                                                         cplx<T>* __restrict__ st, const double* __restrict__ cc) {
+    const T inv_theta = T(cc[0]), dt0 = T(cc[1]);
     for (size_t p = blockIdx.x * (size_t)BLOCK + threadIdx.x; p < N; p += (size_t)gridDim.x * BLOCK) {
         const cplx<T> x = v[p];
         const cplx<T> dd = inv_theta * x, ddt = dt0 * x;
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(BLOCK) void k_chebadj_start(size_t N, const cplx<T>
 // t1 = A d_in and t2 = A dt_in on the tile and a ring of one node in
 // LDS (from d_in, dt_in on a ring of two), then at the tile's nodes
 //   r -= A^H t1; rt -= A^H t2; d_out = c1 d + c2 r; dt_out = c1t d + c1 dt + c2t r + c2 rt;
-//   s += d_out; st += dt_out.
+//   s += d_out; st += dt_out                    (cc = {c1, c2, c1t, c2t}).
 // d_out, dt_out must not alias d_in, dt_in (neighbouring tiles still read them); their
 // ring is written 0.  The LDS of d_in, dt_in is reused for t1, t2.  tiles_of(nx, ny)
 // blocks of 64 x 4 threads.
@@ -265,7 +268,8 @@ __global__ __launch_bounds__(BLOCK) void k_chebadj_fused(Geom G, const T* __rest
                                                          const cplx<T>* __restrict__ dt_in, cplx<T>* __restrict__ d_out,
                                                          cplx<T>* __restrict__ dt_out, cplx<T>* __restrict__ r,
                                                          cplx<T>* __restrict__ rt, cplx<T>* __restrict__ s,
-                                                         cplx<T>* __restrict__ st, T c1, T c2, T c1t, T c2t) {
+                                                         cplx<T>* __restrict__ st, const double* __restrict__ cc) {
+    const T c1 = T(cc[0]), c2 = T(cc[1]), c1t = T(cc[2]), c2t = T(cc[3]);
     constexpr int DW = TX + 4, DH = TY + 4, HW = TX + 2, HH = TY + 2;
     constexpr int NQ1 = (HH * HW + BLOCK - 1) / BLOCK;
     __shared__ cplx<T> sa[DH * DW];  // d_in (ring 2), then t1 (ring 1, width HW)
