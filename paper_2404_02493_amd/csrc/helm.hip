@@ -23,6 +23,7 @@
 #include "kernels_tail.hpp"
 #include "kernels_adrfuse.hpp"
 #include "kernels_chebm.hpp"
+#include "kernels_fine.hpp"
 #include "kernels_adjoint.hpp"
 #include "kernels_wtail.hpp"
 #include "kernels_eik.hpp"
@@ -603,36 +604,51 @@ struct Engine {
         WaveLevel& W = c->wl[1];
         const Geom& G = W.G;
         const double* w0 = c->cdev->la;  // la[0]: the Jacobi weight of this problem
-        if (u_in == nullptr) {
-            // the zero-start Jacobi sweep is recomputed inside the restriction and the
-            // post-smoother instead of being stored
+        // from zero on large grids: the row marches (measured in kernels_fine.hpp)
+        if (u_in || (size_t)G.nx * G.ny < (size_t)2048 * 2048) {
+            auto go = [&](auto zc, auto tc) {
+                constexpr bool Z = decltype(zc)::value;
+                using Tc = decltype(tc);
+                const int nt = fuse_tiles(G.nx, G.ny, FINE_FT);
+                const double bc = sizeof(cplx<Tc>) * NN2(G.nx / 2, G.ny / 2);
+                LAUNCH(c, ((Z ? 1 : 3) * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc, (k_fine_down<T, Tc, Z>), dim3(nt),
+                       dim3(FINE_DOWN<Z>), st, G, (const T*)W.n2, (const C*)g, (const C*)u_in, w0, (C*)c->ws1,
+                       (cplx<Tc>*)c->wl[2].g);
+                cycle_coarse(2);
+                LAUNCH(c, ((Z ? 2 : 3) * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc, (k_fine_up<T, Tc, Z>), dim3(nt),
+                       dim3(FINE_UP), st, G, (const T*)W.n2, (const C*)g, (const C*)c->ws1, (const cplx<Tc>*)c->wl[2].u,
+                       w0, (C*)u_out);
+            };
             const bool c64 = c->wl[2].f64;
-            const double bc = c64 ? 16.0 : sizeof(C);
-            if (c64)
-                LAUNCH(c, (sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_restrict<T, double>),
-                       dim3(jac0r_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g, w0,
-                       (c128*)c->wl[2].g);
-            else
-                LAUNCH(c, (sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_restrict<T, T>),
-                       dim3(jac0r_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g, w0, (C*)c->wl[2].g);
-            cycle_coarse(2);
-            if (c64)
-                LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_prolong_jacobi<double, T>),
-                       dim3(jac0p_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g,
-                       (const c128*)c->wl[2].u, w0, (C*)u_out);
-            else
-                LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_prolong_jacobi<T, T>),
-                       dim3(jac0p_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g,
-                       (const C*)c->wl[2].u, w0, (C*)u_out);
+            if (u_in) {
+                if (c64) go(std::false_type{}, double{});
+                else go(std::false_type{}, T{});
+            } else {
+                if (c64) go(std::true_type{}, double{});
+                else go(std::true_type{}, T{});
+            }
             return;
         }
-        LAUNCH(c, ((u_in ? 3 : 2) * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny), (k_jacobi<T>), dim3(tiles_of(G.nx, G.ny)), tile_block(), st, G, (const T*)W.n2,
-                           (const C*)g, (const C*)u_in, (C*)c->ws1, w0);
-        restrict_down(1, g, c->ws1, c->wl[2].g);
+        // the zero-start Jacobi sweep is recomputed inside the restriction and the
+        // post-smoother instead of being stored
+        const bool c64 = c->wl[2].f64;
+        const double bc = c64 ? 16.0 : sizeof(C);
+        if (c64)
+            LAUNCH(c, (sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_restrict<T, double>),
+                   dim3(jac0r_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g, w0,
+                   (c128*)c->wl[2].g);
+        else
+            LAUNCH(c, (sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_restrict<T, T>),
+                   dim3(jac0r_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g, w0, (C*)c->wl[2].g);
         cycle_coarse(2);
-        prolong_up(1, c->wl[2].u, c->ws1);
-        LAUNCH(c, (3 * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny), (k_jacobi<T>), dim3(tiles_of(G.nx, G.ny)), tile_block(), st, G, (const T*)W.n2,
-                           (const C*)g, (const C*)c->ws1, (C*)u_out, w0);
+        if (c64)
+            LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_prolong_jacobi<double, T>),
+                   dim3(jac0p_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g,
+                   (const c128*)c->wl[2].u, w0, (C*)u_out);
+        else
+            LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(G.nx, G.ny) + bc * NN2(G.nx / 2, G.ny / 2), (k_jac0_prolong_jacobi<T, T>),
+                   dim3(jac0p_units(G.nx, G.ny)), dim3(64), st, G, (const T*)W.n2, (const C*)g,
+                   (const C*)c->wl[2].u, w0, (C*)u_out);
     }
 
     // ---- ADR corrections on level 2 (M = adr_steps of them)
