@@ -50,96 +50,6 @@ struct FuseCfg<32> {
     static constexpr int DOWN = 896, UP = 832, START = 832, STEP = 768, LAST = 768;
 };
 
-// 1 / sqrt(x) for positive normal x: the hardware approximation and one third-order step
-// y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, in fused multiply-adds.
-__device__ __forceinline__ double rsqrt64(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
-// The normalised normal equations of sstep_small_solve with reciprocal square roots in
-// place of its square roots and divisions (a third of its serial chain).  y[2 j], y[2 j + 1]:
-// coefficient of K_j, zero for columns after the first negligible pivot.
-template <int M>
-__device__ __forceinline__ void fuse_solve(const double* __restrict__ s, double breakdown_tol, double (&y)[2 * M]) {
-    double gr[M + 1][M + 1], gi[M + 1][M + 1];
-    {
-        int o = M + 1;
-#pragma unroll
-        for (int i = 0; i <= M; ++i) {
-            gr[i][i] = s[i];
-            gi[i][i] = 0.0;
-#pragma unroll
-            for (int j = i + 1; j <= M; ++j) {
-                gr[i][j] = gr[j][i] = s[o];
-                gi[i][j] = s[o + 1];
-                gi[j][i] = -s[o + 1];
-                o += 2;
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 2 * M; ++q) y[q] = 0.0;
-    if (!(gr[0][0] > 0.0) || !isfinite(gr[0][0])) return;
-    double rd[M + 1];
-#pragma unroll
-    for (int i = 0; i <= M; ++i) rd[i] = gr[i][i] > 0.0 ? rsqrt64(gr[i][i]) : 0.0;
-    const double d0 = gr[0][0] * rd[0];
-    double Lr[M][M], Li[M][M], il[M], zr[M], zi[M];
-    bool keep[M];
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        // column j of N = L L^H, N(i, j) = G(i + 1, j + 1) rd rd
-        double p = gr[j + 1][j + 1] * rd[j + 1] * rd[j + 1];
-#pragma unroll
-        for (int q = 0; q < j; ++q) p -= Lr[j][q] * Lr[j][q] + Li[j][q] * Li[j][q];
-        ok = ok && (p > breakdown_tol * breakdown_tol);
-        keep[j] = ok;
-        il[j] = ok ? rsqrt64(p) : 1.0;
-#pragma unroll
-        for (int i = j + 1; i < M; ++i) {
-            const double sc = rd[i + 1] * rd[j + 1];
-            double sr = gr[i + 1][j + 1] * sc, si = gi[i + 1][j + 1] * sc;
-#pragma unroll
-            for (int q = 0; q < j; ++q) {
-                sr -= Lr[i][q] * Lr[j][q] + Li[i][q] * Li[j][q];
-                si -= Li[i][q] * Lr[j][q] - Lr[i][q] * Li[j][q];
-            }
-            Lr[i][j] = sr * il[j];
-            Li[i][j] = si * il[j];
-        }
-        // L z = r, r(j) = G(j + 1, 0) rd rd
-        const double sc = rd[j + 1] * rd[0];
-        double sr = gr[j + 1][0] * sc, si = gi[j + 1][0] * sc;
-#pragma unroll
-        for (int q = 0; q < j; ++q) {
-            sr -= Lr[j][q] * zr[q] - Li[j][q] * zi[q];
-            si -= Lr[j][q] * zi[q] + Li[j][q] * zr[q];
-        }
-        zr[j] = keep[j] ? sr * il[j] : 0.0;
-        zi[j] = keep[j] ? si * il[j] : 0.0;
-    }
-#pragma unroll
-    for (int i = M - 1; i >= 0; --i) {  // L^H c' = z
-        double sr = zr[i], si = zi[i];
-#pragma unroll
-        for (int q = i + 1; q < M; ++q) {
-            sr -= Lr[q][i] * zr[q] + Li[q][i] * zi[q];
-            si -= Lr[q][i] * zi[q] - Li[q][i] * zr[q];
-        }
-        zr[i] = keep[i] ? sr * il[i] : 0.0;
-        zi[i] = keep[i] ? si * il[i] : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) {  // c_j = c'_j d_0 / d_j
-        const double sc = keep[i] ? d0 * rd[i + 1] : 0.0;
-        y[2 * i] = zr[i] * sc;
-        y[2 * i + 1] = zi[i] * sc;
-    }
-}
-
 // The coefficients c_1..c_3 of the smoother that the previous kernel's ng Gram partials
 // belong to (ng <= FUSE_FOLD): fuse_coef_sums adds them up (one wavefront per entry, a
 // fixed order), fuse_coef_solve (after a barrier) solves in the last wavefront,
@@ -159,7 +69,9 @@ template <int FB>
 __device__ __forceinline__ void fuse_coef_solve(double* sh) {
     if (threadIdx.x < FB - 64) return;
     double y[6];
-    fuse_solve<3>(sh, 1e-12, y);
+    double beta;
+    int cols;
+    sstep_small_solve<3>(sh, 1e-12, y, cols, beta);
     if (threadIdx.x == FB - 1) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) sh[16 + q] = y[q];

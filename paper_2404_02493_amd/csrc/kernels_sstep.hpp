@@ -340,118 +340,111 @@ __global__ __launch_bounds__(64) void k_sstep_gram(AdrGeom A, int S, const T* __
         if (!(own_lane && j <= A.nx - 1)) return;
         gram_add<T, M>(acc, k);
     });
+    if constexpr (NG == 16) {
+        const double sum = wave_sum16(acc);
+        if (!(lane & 3)) partials[(size_t)(lane >> 2) * gridDim.x + blockIdx.x] = sum;
+    } else {
 #pragma unroll
-    for (int v = 0; v < NG; ++v) {
-        const double sum = wave_sum(acc[v]);
-        if (lane == 0) partials[(size_t)v * gridDim.x + blockIdx.x] = sum;
+        for (int v = 0; v < NG; ++v) {
+            const double sum = wave_sum(acc[v]);
+            if (lane == 0) partials[(size_t)v * gridDim.x + blockIdx.x] = sum;
+        }
     }
 }
 
+// 1 / sqrt(x) for positive normal x: the hardware approximation and one third-order step
+// y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, in fused multiply-adds.
+__device__ __forceinline__ double rsqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // Normalised Cholesky solve of the normal equations from the Gram sums (layout of
-// k_sstep_gram); one thread.  yr, yi: coefficients c_j of K_{j-1}; cols: columns kept
-// (columns after the first negligible pivot are dropped); beta = ||K_0||.
+// k_sstep_gram); one thread.  y[2 j], y[2 j + 1]: coefficient of K_j, zero for the columns
+// after the first negligible pivot; cols: columns kept; beta = ||K_0||.  The serial chain is
+// what it costs, so reciprocal square roots stand in for square roots and divisions.
 template <int M>
-__device__ __forceinline__ void sstep_small_solve(const double* __restrict__ sums, double breakdown_tol,
-                                                  double (&yr)[M], double (&yi)[M], int& cols, double& beta) {
-    // Hermitian G(i,j), i,j = 0..M; every loop below has compile-time bounds so that
-    // the small arrays stay in registers.
+__device__ __forceinline__ void sstep_small_solve(const double* __restrict__ s, double breakdown_tol,
+                                                  double (&y)[2 * M], int& cols, double& beta) {
     double gr[M + 1][M + 1], gi[M + 1][M + 1];
-#pragma unroll
-    for (int i = 0; i <= M; ++i) {
-        gr[i][i] = sums[i];
-        gi[i][i] = 0.0;
-    }
     {
         int o = M + 1;
 #pragma unroll
-        for (int i = 0; i <= M; ++i)
+        for (int i = 0; i <= M; ++i) {
+            gr[i][i] = s[i];
+            gi[i][i] = 0.0;
 #pragma unroll
             for (int j = i + 1; j <= M; ++j) {
-                gr[i][j] = sums[o];
-                gi[i][j] = sums[o + 1];
-                gr[j][i] = sums[o];
-                gi[j][i] = -sums[o + 1];
+                gr[i][j] = gr[j][i] = s[o];
+                gi[i][j] = s[o + 1];
+                gi[j][i] = -s[o + 1];
                 o += 2;
             }
+        }
     }
-    beta = sqrt(gr[0][0]);
 #pragma unroll
-    for (int i = 0; i < M; ++i) yr[i] = yi[i] = 0.0;
+    for (int q = 0; q < 2 * M; ++q) y[q] = 0.0;
     cols = 0;
-    if (beta > 0.0 && isfinite(beta)) {
-        // reciprocals up front: one thread runs this, so the serial chain of divisions
-        // and square roots is what it costs
-        double d[M + 1], rd[M + 1];
+    beta = gr[0][0];  // 0 or not finite: no columns
+    if (!(gr[0][0] > 0.0) || !isfinite(gr[0][0])) return;
+    double rd[M + 1];
 #pragma unroll
-        for (int i = 0; i <= M; ++i) {
-            d[i] = sqrt(gr[i][i]);
-            rd[i] = d[i] > 0 ? 1.0 / d[i] : 0.0;
-        }
-        // normalised normal equations N c' = r, N(i,j) = G(i,j)/(d_i d_j), r(i) = G(i,0)/(d_i d_0)
-        double Lr[M][M], Li[M][M], il[M];
+    for (int i = 0; i <= M; ++i) rd[i] = gr[i][i] > 0.0 ? rsqrt64(gr[i][i]) : 0.0;
+    const double d0 = gr[0][0] * rd[0];
+    beta = d0;
+    double Lr[M][M], Li[M][M], il[M], zr[M], zi[M];
+    bool keep[M];
+    bool ok = true;
 #pragma unroll
-        for (int i = 0; i < M; ++i)
+    for (int j = 0; j < M; ++j) {
+        // column j of N = L L^H, N(i, j) = G(i + 1, j + 1) rd rd
+        double p = gr[j + 1][j + 1] * rd[j + 1] * rd[j + 1];
 #pragma unroll
-            for (int j = 0; j < M; ++j) {
-                const double sc = rd[i + 1] * rd[j + 1];
-                Lr[i][j] = gr[i + 1][j + 1] * sc;
-                Li[i][j] = gi[i + 1][j + 1] * sc;
+        for (int q = 0; q < j; ++q) p -= Lr[j][q] * Lr[j][q] + Li[j][q] * Li[j][q];
+        ok = ok && (p > breakdown_tol * breakdown_tol);
+        keep[j] = ok;
+        if (ok) cols = j + 1;
+        il[j] = ok ? rsqrt64(p) : 1.0;
+#pragma unroll
+        for (int i = j + 1; i < M; ++i) {
+            const double sc = rd[i + 1] * rd[j + 1];
+            double sr = gr[i + 1][j + 1] * sc, si = gi[i + 1][j + 1] * sc;
+#pragma unroll
+            for (int q = 0; q < j; ++q) {
+                sr -= Lr[i][q] * Lr[j][q] + Li[i][q] * Li[j][q];
+                si -= Li[i][q] * Lr[j][q] - Lr[i][q] * Li[j][q];
             }
-        // Cholesky N = L L^H; columns after the first negligible pivot are dropped
-        bool ok = true;
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-            double p = Lr[j][j];
-#pragma unroll
-            for (int q = 0; q < j; ++q) p -= Lr[j][q] * Lr[j][q] + Li[j][q] * Li[j][q];
-            ok = ok && (p > breakdown_tol * breakdown_tol);
-            if (ok) cols = j + 1;
-            const double lj = ok ? sqrt(p) : 1.0;
-            il[j] = 1.0 / lj;
-            Lr[j][j] = lj;
-            Li[j][j] = 0.0;
-#pragma unroll
-            for (int i = j + 1; i < M; ++i) {
-                double sr = Lr[i][j], si = Li[i][j];
-#pragma unroll
-                for (int q = 0; q < j; ++q) {
-                    sr -= Lr[i][q] * Lr[j][q] + Li[i][q] * Li[j][q];
-                    si -= Li[i][q] * Lr[j][q] - Lr[i][q] * Li[j][q];
-                }
-                Lr[i][j] = sr * il[j];
-                Li[i][j] = si * il[j];
-            }
+            Lr[i][j] = sr * il[j];
+            Li[i][j] = si * il[j];
         }
-        double zr[M], zi[M];
+        // L z = r, r(j) = G(j + 1, 0) rd rd
+        const double sc = rd[j + 1] * rd[0];
+        double sr = gr[j + 1][0] * sc, si = gi[j + 1][0] * sc;
 #pragma unroll
-        for (int i = 0; i < M; ++i) {  // L z = r  (rows >= cols give zero)
-            const double sc = rd[i + 1] * rd[0];
-            double sr = gr[i + 1][0] * sc, si = gi[i + 1][0] * sc;
-#pragma unroll
-            for (int q = 0; q < i; ++q) {
-                sr -= Lr[i][q] * zr[q] - Li[i][q] * zi[q];
-                si -= Lr[i][q] * zi[q] + Li[i][q] * zr[q];
-            }
-            zr[i] = i < cols ? sr * il[i] : 0.0;
-            zi[i] = i < cols ? si * il[i] : 0.0;
+        for (int q = 0; q < j; ++q) {
+            sr -= Lr[j][q] * zr[q] - Li[j][q] * zi[q];
+            si -= Lr[j][q] * zi[q] + Li[j][q] * zr[q];
         }
+        zr[j] = keep[j] ? sr * il[j] : 0.0;
+        zi[j] = keep[j] ? si * il[j] : 0.0;
+    }
 #pragma unroll
-        for (int i = M - 1; i >= 0; --i) {  // L^H c' = z
-            double sr = zr[i], si = zi[i];
+    for (int i = M - 1; i >= 0; --i) {  // L^H c' = z
+        double sr = zr[i], si = zi[i];
 #pragma unroll
-            for (int q = i + 1; q < M; ++q) {
-                sr -= Lr[q][i] * zr[q] + Li[q][i] * zi[q];
-                si -= Lr[q][i] * zi[q] - Li[q][i] * zr[q];
-            }
-            zr[i] = i < cols ? sr * il[i] : 0.0;
-            zi[i] = i < cols ? si * il[i] : 0.0;
+        for (int q = i + 1; q < M; ++q) {
+            sr -= Lr[q][i] * zr[q] + Li[q][i] * zi[q];
+            si -= Lr[q][i] * zi[q] - Li[q][i] * zr[q];
         }
+        zr[i] = keep[i] ? sr * il[i] : 0.0;
+        zi[i] = keep[i] ? si * il[i] : 0.0;
+    }
 #pragma unroll
-        for (int i = 0; i < M; ++i) {  // c_j = c'_j d_0 / d_j
-            const double sc = i < cols ? d[0] * rd[i + 1] : 0.0;
-            yr[i] = zr[i] * sc;
-            yi[i] = zi[i] * sc;
-        }
+    for (int i = 0; i < M; ++i) {  // c_j = c'_j d_0 / d_j
+        const double sc = keep[i] ? d0 * rd[i + 1] : 0.0;
+        y[2 * i] = zr[i] * sc;
+        y[2 * i + 1] = zi[i] * sc;
     }
 }
 
@@ -499,18 +492,12 @@ __global__ __launch_bounds__(SOLVE_THREADS) void k_sstep_solve(const double* __r
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    double g[NG];
-#pragma unroll
-    for (int q = 0; q < NG; ++q) g[q] = sums[q];
-    double yr[M], yi[M], beta;
+    double y[2 * M], beta;
     int cols;
-    sstep_small_solve<M>(g, breakdown_tol, yr, yi, cols, beta);
+    sstep_small_solve<M>(sums, breakdown_tol, y, cols, beta);
     K->beta = beta;
 #pragma unroll
-    for (int j = 0; j < M; ++j) {
-        K->y[2 * j] = yr[j];
-        K->y[2 * j + 1] = yi[j];
-    }
+    for (int j = 0; j < 2 * M; ++j) K->y[j] = y[j];
     K->cols = cols;
     K->done = isfinite(beta) ? 1 : 2;
 }
@@ -880,8 +867,21 @@ __global__ __launch_bounds__(BLOCK) void k_sstep_gram_tile(AdrGeom A, const T* _
                                    [&](int, int, int, bool own, cplx<T>, const cplx<T>(&k)[M + 1]) {
                                        if (own) gram_add<T, M>(acc, k);
                                    });
-    block_sum<NG, BLOCK / 64>(acc, NG, red, sums);
-    store_partials(sums, NG, partials);
+    if constexpr (NG == 16) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const double s = wave_sum16(acc);
+        if (!(lane & 3)) red[wave * 16 + (lane >> 2)] = s;
+        __syncthreads();
+        if (threadIdx.x < 16) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < BLOCK / 64; ++w) t += red[w * 16 + threadIdx.x];
+            partials[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+        }
+    } else {
+        block_sum<NG, BLOCK / 64>(acc, NG, red, sums);
+        store_partials(sums, NG, partials);
+    }
 }
 
 // Pass 2 in tile form with the EPI_X epilogue: xout = x0 + sum c_j K_{j-1} on the own

@@ -120,17 +120,26 @@ __device__ __forceinline__ double group_row_sum(const double* __restrict__ row, 
     constexpr int NW = FBLOCK / 64;
     const int ng = (nblk + 63) / 64 < NW ? (nblk + 63) / 64 : NW;  // groups holding blocks
     double t[NW];
+    if (nblk <= FBLOCK) {
 #pragma unroll
-    for (int g = 0; g < NW; ++g) {  // the first FBLOCK blocks: every load issued (from
-        const int bb = g * 64 + lane;  // block 0 past the end), none under a branch
-        const double v = row[bb < nblk ? bb : 0];
-        t[g] = bb < nblk ? 0.0 + v : 0.0;
-    }
-    for (int b0 = FBLOCK; b0 < nblk; b0 += FBLOCK) {
+        for (int g = 0; g < NW; ++g) {  // every load issued (from block 0 past the end), none
+            const int bb = g * 64 + lane;  // under a branch
+            const double v = row[bb < nblk ? bb : 0];
+            t[g] = bb < nblk ? 0.0 + v : 0.0;
+        }
+    } else {  // FBLOCK < nblk <= 2 FBLOCK = MAXRED: both shares of a group in flight at once
+        static_assert(MAXRED == 2 * FBLOCK, "at most two blocks a lane and group");
+        double t2[NW];
 #pragma unroll
         for (int g = 0; g < NW; ++g) {
-            const int bb = b0 + g * 64 + lane;
-            if (bb < nblk) t[g] += row[bb];
+            const int bb = FBLOCK + g * 64 + lane;
+            t[g] = row[g * 64 + lane];
+            t2[g] = row[bb < nblk ? bb : 0];
+        }
+#pragma unroll
+        for (int g = 0; g < NW; ++g) {
+            t[g] = 0.0 + t[g];
+            if (FBLOCK + g * 64 + lane < nblk) t[g] += t2[g];
         }
     }
     double sv = 0.0;
