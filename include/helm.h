@@ -89,7 +89,8 @@ typedef struct {
                                  in s-step form on every level, no tuned form, small grids */
     int32_t wave_tail_n;      /* the wave levels >= 3 with at most wave_tail_n nodes on the longer side (and at
                                  most 4096 nodes) run in one workgroup, all of them in a single launch
-                                 (default 32; 0 = never); an unsmoothed level 3 joins those below it */
+                                 (default 32; 0 = never); an unsmoothed level 3 joins those below it, and
+                                 a coarsest level of at most 4096 nodes runs so by itself unless 0 */
     double shift;             /* relative imaginary shift s0 >= 0 of the shifted equation (Section 4.3.2,
                                  gamma_0 = s0 k(x)^2 with k(x) = k n(x); the paper's test uses 0.01):
                                  kappa = k^2 n^2 (1 + i sigma (delta + s0)); default 0 */

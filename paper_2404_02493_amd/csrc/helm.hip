@@ -324,6 +324,9 @@ static inline double NN2(int nx, int ny) { return double(nx) * double(ny); }
 static size_t csize(bool f64) { return f64 ? sizeof(c128) : sizeof(c64); }
 static size_t rsize(bool f64) { return f64 ? sizeof(double) : sizeof(float); }
 
+// A level of nx x ny nodes can be the first one of the one-workgroup wave kernel.
+static bool wave_tail_fits(int nx, int ny) { return (size_t)nx * ny <= WT_NODES && std::max(nx, ny) <= WT_ROW; }
+
 static int nv_bucket(int m) { return m <= 4 ? 4 : (m <= 12 ? 12 : MAXM); }
 
 // ------------------------------------------------------------------ default weights
@@ -523,9 +526,14 @@ struct Engine {
         });
     }
 
-    // ---- the coarsest wave level (always FP64)
+    // ---- the coarsest wave level (always FP64): in one workgroup when it fits there (64^2:
+    // ten launches of 6 us otherwise)
     void coarsest(int l) {
         WaveLevel& W = c->wl[l];
+        if (c->d.wave_tail_n > 0 && wave_tail_fits(W.nx, W.ny)) {
+            wave_tail(l);
+            return;
+        }
         chebyshev<double>(l, W.g, W.u, true, c->w[l - 1], c->d.cheb_coarse);
     }
 
@@ -700,7 +708,7 @@ struct Engine {
             const double bytes = (3 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny) + (2 * sizeof(C) + 2 * sizeof(T)) * NN2(B.nx, B.ny);
             with_edge(fuse_ft(q), [&](auto e) {
                 constexpr int FT = decltype(e)::value;
-                LAUNCH(c, bytes, (k_fuse_down<T, FT>), dim3(fuse_ng(q)), dim3(FuseCfg<FT>::DOWN), st, A.A, B.A,
+                LAUNCH(c, bytes, (k_fuse_down<T, FT>), dim3(fuse_ng(q)), dim3(FuseCfg<T, FT>::DOWN), st, A.A, B.A,
                        (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b, (const double*)fuse_part(h), np,
                        (C*)A.x, (const T*)B.px, (const T*)B.py, (const C*)B.c0, (C*)B.b, fuse_part(1 - h));
             });
@@ -724,7 +732,7 @@ struct Engine {
         auto go = [&](auto xc, auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, bytes, (k_fuse_up<T, decltype(xc)::value, FT, GRAM>), dim3(fuse_tiles(A.nx, A.ny, FT)),
-                   dim3(FuseCfg<FT>::UP), st, A.A, B.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   dim3(FuseCfg<T, FT>::UP), st, A.A, B.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
                    (const C*)(GRAM ? A.x : pinto), (C*)(GRAM ? A.xalt : pinto), (const T*)B.px, (const T*)B.py,
                    (const C*)B.c0, (const C*)B.b, (const C*)B.x, (const double*)fuse_part(h), np, fuse_part(1 - h));
         };
@@ -750,7 +758,7 @@ struct Engine {
         with_edge(fuse_ft(l), [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (2 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny), (k_fuse_gram<T, FT>), dim3(fuse_ng(l)),
-                   dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   dim3(FuseCfg<T, FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
                    fuse_part(h));
         });
         fuse_down_up(l, h);
@@ -769,14 +777,14 @@ struct Engine {
         int h = 0;
         with_edge(fuse_ft(2), [&](auto e) {
             constexpr int FT = decltype(e)::value;
-            LAUNCH(c, (5 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_start<T, FT>), dim3(ng), dim3(FuseCfg<FT>::START), st,
+            LAUNCH(c, (5 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_start<T, FT>), dim3(ng), dim3(FuseCfg<T, FT>::START), st,
                    A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, mod_args(nullptr, A.b), fuse_part(h));
             for (int s = 0; s < M; ++s) {
                 fuse_down_up(2, h);
                 if (s + 1 < M) {
                     const ModArgs<T> ma = mod_args(W.u == u_home ? W.ualt : u_home, A.b == b_home ? A.balt : b_home);
                     LAUNCH(c, (9 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_step<T, true, FT>), dim3(ng),
-                           dim3(FuseCfg<FT>::STEP), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           dim3(FuseCfg<T, FT>::STEP), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
                            (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, fuse_part(1 - h));
                     std::swap(W.u, W.ualt);
                     std::swap(A.b, A.balt);
@@ -784,7 +792,7 @@ struct Engine {
                 } else {
                     const ModArgs<T> ma = mod_args(u_home, nullptr);
                     LAUNCH(c, (6 * sizeof(C) + 2 * sizeof(T)) * nn, (k_fuse_step<T, false, FT>), dim3(ng),
-                           dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           dim3(FuseCfg<T, FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
                            (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, (double*)nullptr);
                     if (W.u != u_home) std::swap(W.u, W.ualt);
                 }
@@ -1433,10 +1441,7 @@ static void build(helm_ctx c, const double* velocity, hipStream_t st) {
     // first level (>= 3) small enough for the one-workgroup tail of the wave cycle; level 3
     // without smoothing (two transfers) joins a tail that would begin at level 4
     c->LT = 0;
-    auto wt_fits = [&](int l) {
-        const WaveLevel& W = c->wl[l];
-        return (size_t)W.nx * W.ny <= WT_NODES && std::max(W.nx, W.ny) <= WT_ROW;
-    };
+    auto wt_fits = [&](int l) { return wave_tail_fits(c->wl[l].nx, c->wl[l].ny); };
     for (int l = 3; l <= L && L <= WT_MAXL; ++l)
         if (std::max(c->wl[l].nx, c->wl[l].ny) <= d.wave_tail_n && wt_fits(l)) {
             c->LT = l;

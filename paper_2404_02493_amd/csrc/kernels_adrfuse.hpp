@@ -39,14 +39,14 @@ __host__ __device__ inline int fuse_side(int m, int ft) { return (m - 2) / ft + 
 __host__ __device__ inline int fuse_tiles(int nx, int ny, int ft) { return fuse_side(nx, ft) * fuse_side(ny, ft); }
 
 // Threads per block: as few idle ones as the region's nodes allow, at most 1024.
-template <int FT>
+template <typename T, int FT>
 struct FuseCfg;
-template <>
-struct FuseCfg<16> {
+template <typename T>
+struct FuseCfg<T, 16> {
     static constexpr int DOWN = 640, UP = 576, START = 576, STEP = 960, LAST = 512;
 };
-template <>
-struct FuseCfg<32> {
+template <typename T>
+struct FuseCfg<T, 32> {
     static constexpr int DOWN = 896, UP = 832, START = 832, STEP = 768, LAST = 768;
 };
 
@@ -187,13 +187,13 @@ __device__ __forceinline__ void fuse_ring(cplx<T>* __restrict__ x, int nx, int n
 // K_0 - sum_j c_j K_j) on the coarse tile and a ring of 3, K_0..K_3 of the coarse
 // smoother there and its Gram sums.  fuse_tiles(A.nx, A.ny, FT) blocks.
 template <typename T, int FT>
-__global__ __launch_bounds__(FuseCfg<FT>::DOWN) void k_fuse_down(
+__global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
     AdrGeom A, AdrGeom Ac, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const double* __restrict__ part_in, int ng, cplx<T>* __restrict__ xout,
     const T* __restrict__ pxc, const T* __restrict__ pyc, const cplx<T>* __restrict__ c0c, cplx<T>* __restrict__ bc,
     double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, part_in, xout, pxc, pyc, c0c, bc, part_out);
-    constexpr int FB = FuseCfg<FT>::DOWN, TC = FT / 2;
+    constexpr int FB = FuseCfg<T, FT>::DOWN, TC = FT / 2;
     constexpr int HC = 3, RC = TC + 2 * HC;          // coarse region
     constexpr int OF = 2 * HC + 3, RW = 2 * RC + 7;  // fine region, the tile at OF
     using RF = FuseReg<T, RW, FB>;
@@ -217,9 +217,14 @@ __global__ __launch_bounds__(FuseCfg<FT>::DOWN) void k_fuse_down(
     F.load(px, fx);
     F.load(py, fy);
     F.load(c0, cc);
-    G.load(pxc, fxc);
-    G.load(pyc, fyc);
-    G.load(c0c, ccc);
+    // (FP64 tiles of 32 x 32 have no registers to spare for the coarse fields this early)
+    constexpr bool EARLY = sizeof(T) == 4 || FT == 16;
+    auto load_coarse = [&] {
+        G.load(pxc, fxc);
+        G.load(pyc, fyc);
+        G.load(c0c, ccc);
+    };
+    if constexpr (EARLY) load_coarse();
     fuse_coef_sums<FB>(part_in, ng, sh);
     fuse_ring(xout, A.nx, A.ny, ti, tj, FT);
     fuse_ring(bc, Ac.nx, Ac.ny, ti, tj, TC);
@@ -234,19 +239,25 @@ __global__ __launch_bounds__(FuseCfg<FT>::DOWN) void k_fuse_down(
     RF::put(kv[2], s0);  // s0 was last read before the barrier above
     cplx<T> c[3];
     fuse_coef_get(sh, c);
-    __syncthreads();
-    F.apply(s0, kv[3]);
+    // x and the residual K_0 - c_1 K_1 - c_2 K_2 before the last application, which leaves two
+    // vectors instead of four beside it
+    cplx<T> rv[RF::NPT];
 #pragma unroll
     for (int k = 0; k < RF::NPT; ++k) {
-        cplx<T> xv{}, rv = kv[0][k];
+        cplx<T> xv{};
+        rv[k] = kv[0][k];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             xv = xv + c[q] * kv[q][k];
-            rv = rv - c[q] * kv[q + 1][k];
+            if (q < 2) rv[k] = rv[k] - c[q] * kv[q + 1][k];
         }
         if (RF::in(k, OF, OF + FT - 1) && F.ok[k]) st_off(xout, F.p[k], xv);
-        s1[RF::S0 + RF::q(k)] = rv;  // exact on the nodes 3..RW - 4
     }
+    __syncthreads();
+    F.apply(s0, kv[3]);
+#pragma unroll
+    for (int k = 0; k < RF::NPT; ++k) s1[RF::S0 + RF::q(k)] = rv[k] - c[2] * kv[3][k];  // exact on 3..RW - 4
+    if constexpr (!EARLY) load_coarse();
     __syncthreads();
     G.coefs(Ac, fxc, fyc, ccc);
     cplx<T> kc[4][RG::NPT];
@@ -266,13 +277,13 @@ __global__ __launch_bounds__(FuseCfg<FT>::DOWN) void k_fuse_down(
 // Gram sums of the pre-smoother on the first joined level when that is not level 2.
 // fuse_tiles(A.nx, A.ny, FT) blocks.
 template <typename T, int FT>
-__global__ __launch_bounds__(FuseCfg<FT>::LAST) void k_fuse_gram(AdrGeom A, const T* __restrict__ px,
+__global__ __launch_bounds__((FuseCfg<T, FT>::LAST)) void k_fuse_gram(AdrGeom A, const T* __restrict__ px,
                                                                  const T* __restrict__ py,
                                                                  const cplx<T>* __restrict__ c0,
                                                                  const cplx<T>* __restrict__ b,
                                                                  double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, part_out);
-    constexpr int FB = FuseCfg<FT>::LAST, H = 3, RW = FT + 2 * H;
+    constexpr int FB = FuseCfg<T, FT>::LAST, H = 3, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
     __shared__ cplx<T> buf[2 * RF::LB];
     __shared__ double red[FB / 64 * 16];
@@ -297,14 +308,14 @@ __global__ __launch_bounds__(FuseCfg<FT>::LAST) void k_fuse_gram(AdrGeom A, cons
 // fuse_tiles(A.nx, A.ny, FT) blocks; with GRAM xout must not overlap xin (without, the two
 // are one array and xout's ring is left alone).
 template <typename T, bool X0C, int FT, bool GRAM>
-__global__ __launch_bounds__(FuseCfg<FT>::UP) void k_fuse_up(
+__global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
     AdrGeom A, AdrGeom Ac, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const cplx<T>* __restrict__ xin, cplx<T>* __restrict__ xout,
     const T* __restrict__ pxc, const T* __restrict__ pyc, const cplx<T>* __restrict__ c0c,
     const cplx<T>* __restrict__ bc, const cplx<T>* __restrict__ xc, const double* __restrict__ part_in, int ng,
     double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, xin, xout, pxc, pyc, c0c, bc, xc, part_in, part_out);
-    constexpr int FB = FuseCfg<FT>::UP, TC = FT / 2;
+    constexpr int FB = FuseCfg<T, FT>::UP, TC = FT / 2;
     constexpr int H = GRAM ? 4 : 0, RW = FT + 2 * H;  // fine region: fine node 1 + FT ti - H + r
     constexpr int HC = X0C ? 3 : 2, RC = TC + H + 1 + 2 * HC;  // coarse node TC ti - H / 2 - HC + r
     using RF = FuseReg<T, RW, FB>;
@@ -411,12 +422,12 @@ __device__ __forceinline__ void fuse_demod(const RF& R, int i0, int j0, const Mo
 // First ADR step of a cycle: the demodulated residual and the Gram sums of the
 // pre-smoother on level 2.  mod.u read, mod.bout written.
 template <typename T, int FT>
-__global__ __launch_bounds__(FuseCfg<FT>::START) void k_fuse_start(AdrGeom A, const T* __restrict__ px,
+__global__ __launch_bounds__((FuseCfg<T, FT>::START)) void k_fuse_start(AdrGeom A, const T* __restrict__ px,
                                                                    const T* __restrict__ py,
                                                                    const cplx<T>* __restrict__ c0, ModArgs<T> mod,
                                                                    double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, mod, part_out);
-    constexpr int FB = FuseCfg<FT>::START, H = 4, RW = FT + 2 * H;
+    constexpr int FB = FuseCfg<T, FT>::START, H = 4, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
     __shared__ cplx<T> buf[2 * RF::LB];
     __shared__ double red[FB / 64 * 16];
@@ -450,12 +461,12 @@ __global__ __launch_bounds__(FuseCfg<FT>::START) void k_fuse_start(AdrGeom A, co
 // also the demodulated residual of the next ADR step and the Gram sums of its
 // pre-smoother (x on the tile and a ring of 4, the residual on a ring of 3).
 template <typename T, bool NEXT, int FT>
-__global__ __launch_bounds__(NEXT ? FuseCfg<FT>::STEP : FuseCfg<FT>::LAST) void k_fuse_step(
+__global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST)) void k_fuse_step(
     AdrGeom A, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const cplx<T>* __restrict__ x0, const double* __restrict__ part_in, int ng,
     ModArgs<T> mod, double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, x0, part_in, mod, part_out);
-    constexpr int FB = NEXT ? FuseCfg<FT>::STEP : FuseCfg<FT>::LAST;
+    constexpr int FB = NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST;
     constexpr int XH = NEXT ? 4 : 0, H = 3 + XH, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
     __shared__ cplx<T> buf[2 * RF::LB];

@@ -367,31 +367,20 @@ __device__ __forceinline__ double rsqrt64(double x) {
 template <int M>
 __device__ __forceinline__ void sstep_small_solve(const double* __restrict__ s, double breakdown_tol,
                                                   double (&y)[2 * M], int& cols, double& beta) {
-    double gr[M + 1][M + 1], gi[M + 1][M + 1];
-    {
-        int o = M + 1;
-#pragma unroll
-        for (int i = 0; i <= M; ++i) {
-            gr[i][i] = s[i];
-            gi[i][i] = 0.0;
-#pragma unroll
-            for (int j = i + 1; j <= M; ++j) {
-                gr[i][j] = gr[j][i] = s[o];
-                gi[i][j] = s[o + 1];
-                gi[j][i] = -s[o + 1];
-                o += 2;
-            }
-        }
-    }
+    // G(i, j), read where it is used (few registers beside those of a kernel that calls this)
+    auto at = [](int i, int j) { return M + 1 + 2 * (i * (2 * M + 1 - i) / 2 + j - i - 1); };  // i < j
+    auto gr = [&](int i, int j) { return i == j ? s[i] : s[at(i < j ? i : j, i < j ? j : i)]; };
+    auto gi = [&](int i, int j) { return i < j ? s[at(i, j) + 1] : -s[at(j, i) + 1]; };  // i != j
 #pragma unroll
     for (int q = 0; q < 2 * M; ++q) y[q] = 0.0;
     cols = 0;
-    beta = gr[0][0];  // 0 or not finite: no columns
-    if (!(gr[0][0] > 0.0) || !isfinite(gr[0][0])) return;
+    const double g00 = s[0];
+    beta = g00;  // 0 or not finite: no columns
+    if (!(g00 > 0.0) || !isfinite(g00)) return;
     double rd[M + 1];
 #pragma unroll
-    for (int i = 0; i <= M; ++i) rd[i] = gr[i][i] > 0.0 ? rsqrt64(gr[i][i]) : 0.0;
-    const double d0 = gr[0][0] * rd[0];
+    for (int i = 0; i <= M; ++i) rd[i] = s[i] > 0.0 ? rsqrt64(s[i]) : 0.0;
+    const double d0 = g00 * rd[0];
     beta = d0;
     double Lr[M][M], Li[M][M], il[M], zr[M], zi[M];
     bool keep[M];
@@ -399,7 +388,7 @@ __device__ __forceinline__ void sstep_small_solve(const double* __restrict__ s, 
 #pragma unroll
     for (int j = 0; j < M; ++j) {
         // column j of N = L L^H, N(i, j) = G(i + 1, j + 1) rd rd
-        double p = gr[j + 1][j + 1] * rd[j + 1] * rd[j + 1];
+        double p = s[j + 1] * rd[j + 1] * rd[j + 1];
 #pragma unroll
         for (int q = 0; q < j; ++q) p -= Lr[j][q] * Lr[j][q] + Li[j][q] * Li[j][q];
         ok = ok && (p > breakdown_tol * breakdown_tol);
@@ -409,7 +398,7 @@ __device__ __forceinline__ void sstep_small_solve(const double* __restrict__ s, 
 #pragma unroll
         for (int i = j + 1; i < M; ++i) {
             const double sc = rd[i + 1] * rd[j + 1];
-            double sr = gr[i + 1][j + 1] * sc, si = gi[i + 1][j + 1] * sc;
+            double sr = gr(i + 1, j + 1) * sc, si = gi(i + 1, j + 1) * sc;
 #pragma unroll
             for (int q = 0; q < j; ++q) {
                 sr -= Lr[i][q] * Lr[j][q] + Li[i][q] * Li[j][q];
@@ -420,7 +409,7 @@ __device__ __forceinline__ void sstep_small_solve(const double* __restrict__ s, 
         }
         // L z = r, r(j) = G(j + 1, 0) rd rd
         const double sc = rd[j + 1] * rd[0];
-        double sr = gr[j + 1][0] * sc, si = gi[j + 1][0] * sc;
+        double sr = gr(j + 1, 0) * sc, si = gi(j + 1, 0) * sc;
 #pragma unroll
         for (int q = 0; q < j; ++q) {
             sr -= Lr[j][q] * zr[q] - Li[j][q] * zi[q];
