@@ -49,22 +49,48 @@ template <typename T>
 struct FuseCfg<T, 32> {
     static constexpr int DOWN = 896, UP = 832, START = 832, STEP = 768, LAST = 768;
 };
+template <typename T>
+struct FuseCfg<T, 64> {  // k_fuse_up without Gram sums only
+    static constexpr int UP = 768;
+};
 
 // The coefficients c_1..c_3 of the smoother that the previous kernel's ng Gram partials
-// belong to (ng <= FUSE_FOLD): fuse_coef_sums adds them up (one wavefront per entry, a
+// belong to (ng <= FUSE_FOLD): FuseSums adds them up (one wavefront per entry, a
 // fixed order), fuse_coef_solve (after a barrier) solves in the last wavefront,
 // fuse_coef_get (after another) reads.  sh: FUSE_SH doubles of LDS.
 constexpr int FUSE_SH = 22;
+// (the loads come first in a kernel, then those of its fields, then the sums: the
+// coefficients are the longest chain of a pass)
 template <int FB>
-__device__ __forceinline__ void fuse_coef_sums(const double* __restrict__ part, int ng, double* sh) {
-    const int lane = threadIdx.x & 63;
-    for (int v = threadIdx.x >> 6; v < 16; v += FB / 64) {
-        const double* __restrict__ row = part + (size_t)v * ng;
-        const double s =
-            wave_sum(ng <= 64 ? lane_row_sum<1>(row, ng, lane) : lane_row_sum<FUSE_FOLD / 64>(row, ng, lane));
-        if (lane == 0) sh[v] = s;
+struct FuseSums {
+    static constexpr int NW = FB / 64, R = (16 + NW - 1) / NW, SB = FUSE_FOLD / 64;
+    double t[R][SB];
+    __device__ __forceinline__ FuseSums(const double* __restrict__ part, int ng) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int v = wave + r * NW < 16 ? wave + r * NW : 15;
+            const double* __restrict__ row = part + (size_t)v * ng;
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                const int b = k * 64 + lane;
+                const double x = row[b < ng ? b : 0];
+                t[r][k] = b < ng ? x : 0.0;
+            }
+        }
     }
-}
+    __device__ __forceinline__ void sum(double* sh) const {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            double a = t[r][0];
+#pragma unroll
+            for (int k = 1; k < SB; ++k) a += t[r][k];
+            const double s = wave_sum(a);
+            if (lane == 0 && wave + r * NW < 16) sh[wave + r * NW] = s;
+        }
+    }
+};
 template <int FB>
 __device__ __forceinline__ void fuse_coef_solve(double* sh) {
     if (threadIdx.x < FB - 64) return;
@@ -207,6 +233,7 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - OF, j0 = 1 + tj * FT - OF;
     const int I0 = 1 + ti * TC - HC, J0 = 1 + tj * TC - HC;  // 2 I0 = i0 + 4
+    const FuseSums<FB> cs(part_in, ng);
     RF F;
     RG G;
     F.place(A, i0, j0);
@@ -225,7 +252,7 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
         G.load(c0c, ccc);
     };
     if constexpr (EARLY) load_coarse();
-    fuse_coef_sums<FB>(part_in, ng, sh);
+    cs.sum(sh);
     fuse_ring(xout, A.nx, A.ny, ti, tj, FT);
     fuse_ring(bc, Ac.nx, Ac.ny, ti, tj, TC);
     F.coefs(A, fx, fy, cc);
@@ -320,7 +347,7 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
     constexpr int HC = X0C ? 3 : 2, RC = TC + H + 1 + 2 * HC;  // coarse node TC ti - H / 2 - HC + r
     using RF = FuseReg<T, RW, FB>;
     using RG = FuseReg<T, RC, FB>;
-    constexpr int LB = RG::LB > RF::LB ? RG::LB : RF::LB;
+    constexpr int LB = !GRAM || RG::LB > RF::LB ? RG::LB : RF::LB;
     __shared__ cplx<T> buf[2 * LB];
     __shared__ cplx<T> xs[RG::NPT * FB];
     __shared__ double sh[FUSE_SH], red[FB / 64 * 16];
@@ -330,6 +357,7 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - H, j0 = 1 + tj * FT - H;
     const int I0 = ti * TC - H / 2 - HC, J0 = tj * TC - H / 2 - HC;
+    const FuseSums<FB> cs(part_in, ng);
     RG G;
     RF F;
     G.place(Ac, I0, J0);
@@ -349,7 +377,7 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
         F.load(c0, cc);
         fuse_ring(xout, A.nx, A.ny, ti, tj, FT);
     }
-    fuse_coef_sums<FB>(part_in, ng, sh);
+    cs.sum(sh);
     G.coefs(Ac, fxc, fyc, ccc);
     if constexpr (X0C) {
         RG::put(x0, s1);
@@ -476,6 +504,7 @@ __global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST
     int ti, tj;
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - H, j0 = 1 + tj * FT - H;
+    const FuseSums<FB> cs(part_in, ng);
     RF F;
     F.place(A, i0, j0);
     cplx<T> x[RF::NPT], u[RF::NPT], car[RF::NPT], kk[3][RF::NPT], cc[RF::NPT];
@@ -492,7 +521,7 @@ __global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST
         u[k] = ld_off(mod.u, p);
         car[k] = ld_off(mod.car, p);
     }
-    fuse_coef_sums<FB>(part_in, ng, sh);
+    cs.sum(sh);
     fuse_ring(mod.uout, A.nx, A.ny, ti, tj, FT);
     F.coefs(A, fx, fy, cc);
     RF::put(x, s0);
