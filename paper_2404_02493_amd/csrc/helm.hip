@@ -490,14 +490,14 @@ struct Engine {
     template <int FT>
     using ChebType = std::conditional_t<FT <= 32, double, T>;
     bool cheb_passes() const { return c->d.cheb_pre <= CHEBM && c->d.cheb_post <= CHEBM; }
-    // f(tile edge) for level l: 16 while that is at most one block per CU, then 32, then 62 in
-    // FP32 (the largest whose buffers fit the LDS with whole wavefronts busy).
+    // f(tile edge) for level l: 16 while that is at most one block per CU, then 32, then 64 in
+    // FP32 (134 KB of LDS, one block per CU: a level of 1024^2 is one wave of 256 blocks).
     template <typename F>
     void with_cheb_edge(int l, F&& f) const {
         const int nx = c->wl[l].nx, ny = c->wl[l].ny;
         if (fuse_tiles(nx, ny, 16) <= 256) return f(std::integral_constant<int, 16>{});
         if constexpr (sizeof(T) == 4)
-            if (fuse_tiles(nx, ny, 32) > 256) return f(std::integral_constant<int, 62>{});
+            if (fuse_tiles(nx, ny, 32) > 256) return f(std::integral_constant<int, 64>{});
         f(std::integral_constant<int, 32>{});
     }
     // u = Chebyshev(0, g_l), g_{l+1} = R (g_l - A u)
@@ -508,7 +508,7 @@ struct Engine {
         with_cheb_edge(l, [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (2 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
-                   (k_cheb_down<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (k_cheb_down<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::DOWN), st, W.G,
                    (const T*)W.n2, (const C*)W.g, (C*)u, (cplx<Tc>*)c->wl[l + 1].g, cheb_table(l, m, c->w[l - 1]), m);
         });
     }
@@ -520,7 +520,7 @@ struct Engine {
         with_cheb_edge(l, [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (3 * sizeof(C) + sizeof(T)) * NN2(W.nx, W.ny) + sizeof(cplx<Tc>) * NN2(W.nx / 2, W.ny / 2),
-                   (k_cheb_up<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::FB), st, W.G,
+                   (k_cheb_up<T, Tc, FT, ChebType<FT>>), dim3(fuse_tiles(W.nx, W.ny, FT)), dim3(ChebCfg<FT>::UP), st, W.G,
                    (const T*)W.n2, (const C*)W.g, (const C*)u, (const cplx<Tc>*)c->wl[l + 1].u, (C*)W.u,
                    cheb_table(l, m, c->w[l - 1]), m);
         });

@@ -1,7 +1,7 @@
 """GPU parity of the one-pass Chebyshev smoothings and of the one-workgroup wave tail
 against the FP64 oracle, through the cycle from level 2 and the fine cycle.
 
-Grids: levels smaller than a 16 x 16 tile, of a few, of 32 x 32 and (FP32) 62 x 62 tiles with
+Grids: levels smaller than a 16 x 16 tile, of a few, of 32 x 32 and (FP32) 64 x 64 tiles with
 remainders in both directions; step counts 1, 2, 5 and 6 (the last beyond one pass);
 Algorithm 1's literal level 3; the tail off, from 32 nodes a side and from 64 (several nodes a
 thread), on squares and rectangles.  Tolerances as in the other parity tests: 1e-12 (FP64
