@@ -12,11 +12,12 @@
 // On levels of a few hundred nodes per side a pass is bound by its launch, one memory
 // round trip and the issue time of its vector instructions on the CUs that it occupies,
 // so recomputing the rings that the next operation needs costs less than the launches
-// that it saves.  Measured per kernel (FP32): 6.5-7.5 us on a 128^2 level 2, 9.5-12 us on
-// 512^2 (one 32 x 32 tile per CU), about 4 us of either being launch and first loads; a
-// whole cycle, against separate Gram, solve, combination and transfer launches (15 a step
-// instead of 5): 744 -> 385 us at 128^2 in FP64, 823 -> 395 us at 256^2, 942 -> 645 us at
-// 1024^2 in FP32, 1068 -> 913 us there in FP64.
+// that it saves.  Measured per kernel (FP32): 6-7 us on a 128^2 level 2, 9.5-12 us on
+// 512^2 (one 32 x 32 tile per CU), about 4 us of either being launch and first loads; FP64 on
+// 512^2 11-15 us.  A whole cycle, against separate Gram, solve, combination and transfer
+// launches (15 a step instead of 5): 744 -> 385 us at 128^2 in FP64, 823 -> 395 us at 256^2,
+// 942 -> 645 us at 1024^2 in FP32, 1068 -> 913 us there in FP64 (and 654 -> 550 us when, beside
+// later steps elsewhere, the FP64 kernels stopped spilling).
 //
 // A block owns a tile of FTxFT nodes of the finer level (half of that on the coarser one)
 // and builds the Krylov vectors as sstep_tile does, one vector per barrier in two LDS
@@ -38,7 +39,11 @@ constexpr int FUSE_FOLD = 256;
 __host__ __device__ inline int fuse_side(int m, int ft) { return (m - 2) / ft + 1; }
 __host__ __device__ inline int fuse_tiles(int nx, int ny, int ft) { return fuse_side(nx, ft) * fuse_side(ny, ft); }
 
-// Threads per block: as few idle ones as the region's nodes allow, at most 1024.
+// Threads per block: as few idle ones as the region's nodes allow, at most 1024.  The vectors of
+// DOWN and STEP on 32 x 32 tiles take 120-240 registers: eight wavefronts (two per SIMD, five
+// and four nodes a thread) keep them free of spills (FP64 on 512^2: DOWN with 896 threads
+// of three nodes spilled 36 registers, 21.3 us against 11.8; STEP with 768 spilled 20, 18.4
+// against 15.2; FP32 the same within 0.3 us).
 template <typename T, int FT>
 struct FuseCfg;
 template <typename T>
@@ -47,7 +52,7 @@ struct FuseCfg<T, 16> {
 };
 template <typename T>
 struct FuseCfg<T, 32> {
-    static constexpr int DOWN = 896, UP = 832, START = 832, STEP = 768, LAST = 768;
+    static constexpr int DOWN = 512, UP = 832, START = 832, STEP = 512, LAST = 768;
 };
 template <typename T>
 struct FuseCfg<T, 64> {  // k_fuse_up without Gram sums only
@@ -109,6 +114,31 @@ __device__ __forceinline__ void fuse_coef_get(const double* sh, cplx<T> (&c)[3])
     for (int q = 0; q < 3; ++q) c[q] = mk<T>(T(sh[16 + 2 * q]), T(sh[17 + 2 * q]));
 }
 
+// The (RW + 2) x (RW + 2) nodes of a field from (i0 - 1, j0 - 1) for the first application of a
+// chain: load() issues the loads, put() stores them in rows of RW + 2.  Its ring then takes no
+// slot of the threads in the rest of the chain.
+template <typename T, int RW, int FB>
+struct FuseOuter {
+    static constexpr int W = RW + 2, N = W * W, NPT = (N + FB - 1) / FB;
+    cplx<T> v[NPT];
+    __device__ __forceinline__ void load(const AdrGeom& A, const cplx<T>* __restrict__ a, int i0, int j0) {
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int q = (int)threadIdx.x + k * FB;
+            const int gi = i0 - 1 + (int)((unsigned)q / (unsigned)W), gj = j0 - 1 + (int)((unsigned)q % (unsigned)W);
+            const bool in = q < N && gi >= 1 && gi < A.ny && gj >= 1 && gj < A.nx;
+            v[k] = ld_off(a, in ? (unsigned)(gi * A.nx + gj) : 0u);
+        }
+    }
+    __device__ __forceinline__ void put(cplx<T>* s) const {
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            const int q = (int)threadIdx.x + k * FB;
+            if (q < N) s[q] = v[k];
+        }
+    }
+};
+
 // A region of RW x RW nodes of a level whose node (0, 0) is (i0, j0), over FB threads: thread
 // t owns region nodes t, t + FB, ...  LB: size of an LDS buffer (nodes and margins), S0 the
 // index of node 0 in it.
@@ -149,6 +179,23 @@ struct FuseReg {
 #pragma unroll
         for (int k = 0; k < NPT; ++k)
             if (has(k)) s[S0 + q(k)] = v[k];
+    }
+    // v = M s from a buffer that holds one more node on every side, node 0 of it at s
+    __device__ __forceinline__ void apply_start(const cplx<T>* s, cplx<T> (&v)[NPT], bool sub = false) const {
+        constexpr int W = RW + 2;
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) {
+            if (!has(k)) continue;
+            const cplx<T>* a = s + (row(k) + 1) * W + col(k) + 1;
+            const cplx<T> m = up_apply<T>(cf[k], a[0], a[-1], a[1], a[-W], a[W]);
+            v[k] = sub ? v[k] - m : m;
+        }
+    }
+    // v = the centre nodes of such a buffer
+    __device__ __forceinline__ static void get_start(const cplx<T>* s, cplx<T> (&v)[NPT]) {
+        constexpr int W = RW + 2;
+#pragma unroll
+        for (int k = 0; k < NPT; ++k) v[k] = has(k) ? s[(row(k) + 1) * W + col(k) + 1] : cplx<T>{};
     }
     // v = M s, or v -= M s
     __device__ __forceinline__ void apply(const cplx<T>* s, cplx<T> (&v)[NPT], bool sub = false) const {
@@ -221,18 +268,21 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
     bshift(bi.off(), px, py, c0, b, part_in, xout, pxc, pyc, c0c, bc, part_out);
     constexpr int FB = FuseCfg<T, FT>::DOWN, TC = FT / 2;
     constexpr int HC = 3, RC = TC + 2 * HC;          // coarse region
-    constexpr int OF = 2 * HC + 3, RW = 2 * RC + 7;  // fine region, the tile at OF
+    constexpr int OF = 2 * HC + 2, RW = 2 * RC + 5;  // fine region of K_1.., the tile at OF
+    using RO = FuseOuter<T, RW, FB>;                 // and of K_0
     using RF = FuseReg<T, RW, FB>;
     using RG = FuseReg<T, RC, FB>;
-    static_assert(2 * RG::LB <= RF::LB, "coarse buffers in one fine buffer");
-    __shared__ cplx<T> buf[2 * RF::LB];
+    constexpr int LB = RO::N > RF::LB ? RO::N : RF::LB;
+    static_assert(2 * RG::LB <= LB, "coarse buffers in one fine buffer");
+    static_assert(((RF::NPT * FB - 1) / RW + 3) * RO::W <= 2 * LB, "reads beside the last node");
+    __shared__ cplx<T> buf[2 * LB];
     __shared__ double sh[FUSE_SH], red[FB / 64 * 16];
     cplx<T>* s0 = buf;
-    cplx<T>* s1 = buf + RF::LB;
+    cplx<T>* s1 = buf + LB;
     int ti, tj;
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - OF, j0 = 1 + tj * FT - OF;
-    const int I0 = 1 + ti * TC - HC, J0 = 1 + tj * TC - HC;  // 2 I0 = i0 + 4
+    const int I0 = 1 + ti * TC - HC, J0 = 1 + tj * TC - HC;  // 2 I0 = i0 + 3
     const FuseSums<FB> cs(part_in, ng);
     RF F;
     RG G;
@@ -240,26 +290,23 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
     G.place(Ac, I0, J0);
     cplx<T> kv[4][RF::NPT], cc[RF::NPT], ccc[RG::NPT];
     T fx[RF::NPT], fy[RF::NPT], fxc[RG::NPT], fyc[RG::NPT];
-    F.load(b, kv[0]);
+    RO K0;
+    K0.load(A, b, i0, j0);
     F.load(px, fx);
     F.load(py, fy);
     F.load(c0, cc);
-    // (FP64 tiles of 32 x 32 have no registers to spare for the coarse fields this early)
-    constexpr bool EARLY = sizeof(T) == 4 || FT == 16;
-    auto load_coarse = [&] {
-        G.load(pxc, fxc);
-        G.load(pyc, fyc);
-        G.load(c0c, ccc);
-    };
-    if constexpr (EARLY) load_coarse();
+    G.load(pxc, fxc);
+    G.load(pyc, fyc);
+    G.load(c0c, ccc);
     cs.sum(sh);
     fuse_ring(xout, A.nx, A.ny, ti, tj, FT);
     fuse_ring(bc, Ac.nx, Ac.ny, ti, tj, TC);
     F.coefs(A, fx, fy, cc);
-    RF::put(kv[0], s0);
+    K0.put(s0);
     __syncthreads();
     fuse_coef_solve<FB>(sh);
-    F.apply(s0, kv[1]);
+    RF::get_start(s0, kv[0]);
+    F.apply_start(s0, kv[1]);
     RF::put(kv[1], s1);
     __syncthreads();
     F.apply(s1, kv[2]);
@@ -283,14 +330,13 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
     __syncthreads();
     F.apply(s0, kv[3]);
 #pragma unroll
-    for (int k = 0; k < RF::NPT; ++k) s1[RF::S0 + RF::q(k)] = rv[k] - c[2] * kv[3][k];  // exact on 3..RW - 4
-    if constexpr (!EARLY) load_coarse();
+    for (int k = 0; k < RF::NPT; ++k) s1[RF::S0 + RF::q(k)] = rv[k] - c[2] * kv[3][k];  // exact on 2..RW - 3
     __syncthreads();
     G.coefs(Ac, fxc, fyc, ccc);
     cplx<T> kc[4][RG::NPT];
 #pragma unroll
     for (int k = 0; k < RG::NPT; ++k) {
-        const cplx<T>* r = s1 + RF::S0 + (G.ok[k] ? (2 * RG::row(k) + 4) * RW + 2 * RG::col(k) + 4 : RW + 1);
+        const cplx<T>* r = s1 + RF::S0 + (G.ok[k] ? (2 * RG::row(k) + 3) * RW + 2 * RG::col(k) + 3 : RW + 1);
         const cplx<T> ud = ((r[-RW] + r[RW]) + r[-1]) + r[1];
         const cplx<T> dg = ((r[-RW - 1] + r[-RW + 1]) + r[RW - 1]) + r[RW + 1];
         const cplx<T> v = T(1.0 / 16.0) * ((T(4) * r[0] + T(2) * ud) + dg);
@@ -428,22 +474,23 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
     }
 }
 
-// b = (g - A u) e^{-i theta} at the unknowns lo..hi of the region from u in LDS (su, 0 off
-// the unknowns), 0 elsewhere.
-template <typename RF, typename T>
+// b = (g - A u) e^{-i theta} at the unknowns of the region from u in LDS (0 off the unknowns;
+// rows of W, region node (0, 0) at su), 0 elsewhere.
+template <int W, typename RF, typename T>
 __device__ __forceinline__ void fuse_demod(const RF& R, int i0, int j0, const ModArgs<T>& mod, const cplx<T>* su,
                                            const cplx<T> (&car)[RF::NPT], const cplx<T> (&g)[RF::NPT],
-                                           const T (&n2)[RF::NPT], int lo, int hi, int rw, cplx<T> (&b)[RF::NPT]) {
+                                           const T (&n2)[RF::NPT], cplx<T> (&b)[RF::NPT]) {
     const T ih2 = T(mod.G.inv_h2);
 #pragma unroll
     for (int k = 0; k < RF::NPT; ++k) {
-        const cplx<T>* a = su + RF::S0 + RF::q(k);
+        if (!RF::has(k)) continue;
+        const cplx<T>* a = su + RF::row(k) * W + RF::col(k);
         const cplx<T> cu = a[0];
-        const cplx<T> nb = ((a[-rw] + a[rw]) + a[-1]) + a[1];
+        const cplx<T> nb = ((a[-W] + a[W]) + a[-1]) + a[1];
         const cplx<T> lap = ih2 * (T(4) * cu - nb);
         const cplx<T> kap = kappa_at<T>(mod.G, n2[k], i0 + RF::row(k), j0 + RF::col(k));
         const cplx<T> v = (g[k] - (lap - kap * cu)) * conjg(car[k]);
-        b[k] = RF::in(k, lo, hi) && R.ok[k] ? v : cplx<T>{};
+        b[k] = R.ok[k] ? v : cplx<T>{};
     }
 }
 
@@ -455,18 +502,22 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::START)) void k_fuse_start(AdrGeom 
                                                                    const cplx<T>* __restrict__ c0, ModArgs<T> mod,
                                                                    double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, mod, part_out);
-    constexpr int FB = FuseCfg<T, FT>::START, H = 4, RW = FT + 2 * H;
+    constexpr int FB = FuseCfg<T, FT>::START, H = 3, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
-    __shared__ cplx<T> buf[2 * RF::LB];
+    using RO = FuseOuter<T, RW, FB>;
+    constexpr int LB = RO::N > RF::LB ? RO::N : RF::LB;
+    static_assert(((RF::NPT * FB - 1) / RW + 3) * RO::W <= 2 * LB, "reads beside the last node");
+    __shared__ cplx<T> buf[2 * LB];
     __shared__ double red[FB / 64 * 16];
     int ti, tj;
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - H, j0 = 1 + tj * FT - H;
     RF F;
+    RO U;
     F.place(A, i0, j0);
-    cplx<T> u[RF::NPT], car[RF::NPT], g[RF::NPT], kv[4][RF::NPT], cc[RF::NPT];
+    cplx<T> car[RF::NPT], g[RF::NPT], kv[4][RF::NPT], cc[RF::NPT];
     T n2[RF::NPT], fx[RF::NPT], fy[RF::NPT];
-    F.load(mod.u, u);
+    U.load(A, mod.u, i0, j0);
     F.load(mod.car, car);
     F.load(mod.g, g);
     F.load(mod.n2, n2);
@@ -474,14 +525,14 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::START)) void k_fuse_start(AdrGeom 
     F.load(py, fy);
     F.load(c0, cc);
     fuse_ring(mod.bout, A.nx, A.ny, ti, tj, FT);
-    RF::put(u, buf);
+    U.put(buf);
     __syncthreads();
-    fuse_demod<RF, T>(F, i0, j0, mod, buf, car, g, n2, 1, RW - 2, RW, kv[0]);
+    fuse_demod<RO::W, RF, T>(F, i0, j0, mod, buf + RO::W + 1, car, g, n2, kv[0]);
     F.coefs(A, fx, fy, cc);
 #pragma unroll
     for (int k = 0; k < RF::NPT; ++k)
         if (RF::in(k, H, H + FT - 1) && F.ok[k]) st_off(mod.bout, F.p[k], kv[0][k]);
-    F.template chain<3>(kv, buf + RF::LB, buf);
+    F.template chain<3>(kv, buf + LB, buf);
     F.gram(kv, H, H + FT - 1, red, part_out);
 }
 
@@ -495,21 +546,28 @@ __global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST
     ModArgs<T> mod, double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, x0, part_in, mod, part_out);
     constexpr int FB = NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST;
-    constexpr int XH = NEXT ? 4 : 0, H = 3 + XH, RW = FT + 2 * H;
+    constexpr int XH = NEXT ? 4 : 0, H = 2 + XH, RW = FT + 2 * H;  // region of r = b - M x0
+    constexpr int HN = 3, RN = FT + 2 * HN;                        // and of the next right-hand side
     using RF = FuseReg<T, RW, FB>;
-    __shared__ cplx<T> buf[2 * RF::LB];
+    using RO = FuseOuter<T, RW, FB>;
+    using RS = FuseReg<T, RN, FB>;
+    constexpr int LB = RO::N > RF::LB ? RO::N : RF::LB;
+    static_assert(((RF::NPT * FB - 1) / RW + 3) * RO::W <= 2 * LB, "reads beside the last node");
+    static_assert(!NEXT || (RS::LB <= LB && (RS::NPT * FB - 1) / RN + 3 <= 2 * LB / RW), "next step's vectors");
+    __shared__ cplx<T> buf[2 * LB];
     __shared__ double sh[FUSE_SH], red[NEXT ? FB / 64 * 16 : 1];
     cplx<T>* s0 = buf;
-    cplx<T>* s1 = buf + RF::LB;
+    cplx<T>* s1 = buf + LB;
     int ti, tj;
     tile_index(fuse_side(A.nx, FT), ti, tj);
     const int i0 = 1 + ti * FT - H, j0 = 1 + tj * FT - H;
     const FuseSums<FB> cs(part_in, ng);
     RF F;
+    RO X;
     F.place(A, i0, j0);
     cplx<T> x[RF::NPT], u[RF::NPT], car[RF::NPT], kk[3][RF::NPT], cc[RF::NPT];
     T fx[RF::NPT], fy[RF::NPT];
-    F.load(x0, x);
+    X.load(A, x0, i0, j0);
     F.load(b, kk[0]);
     F.load(px, fx);
     F.load(py, fy);
@@ -524,36 +582,48 @@ __global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST
     cs.sum(sh);
     fuse_ring(mod.uout, A.nx, A.ny, ti, tj, FT);
     F.coefs(A, fx, fy, cc);
-    RF::put(x, s0);
+    X.put(s0);
     __syncthreads();
     fuse_coef_solve<FB>(sh);
-    F.apply(s0, kk[0], true);
+    RF::get_start(s0, x);
+    F.apply_start(s0, kk[0], true);
     F.template chain<2>(kk, s1, s0);
     cplx<T> c[3];
     fuse_coef_get(sh, c);
 #pragma unroll
     for (int k = 0; k < RF::NPT; ++k) {
+        if (!RF::has(k)) continue;
 #pragma unroll
         for (int q = 0; q < 3; ++q) x[k] = x[k] + c[q] * kk[q][k];
         u[k] = u[k] + x[k] * car[k];
         if (RF::in(k, H, H + FT - 1) && F.ok[k]) st_off(mod.uout, F.p[k], u[k]);
     }
     if constexpr (NEXT) {
-        cplx<T> g[RF::NPT], kv[4][RF::NPT];
-        T n2[RF::NPT];
-        F.load(mod.g, g);
-        F.load(mod.n2, n2);
+        // on the smaller region, with fewer nodes a thread, from fields read again (L2; loading
+        // them with the first ones gained nothing in FP32 and spills in FP64)
+        RS S;
+        const int n0 = i0 + H - HN, m0 = j0 + H - HN;
+        S.place(A, n0, m0);
+        cplx<T> g[RS::NPT], cr[RS::NPT], c0s[RS::NPT], kv[4][RS::NPT];
+        T n2[RS::NPT], fxs[RS::NPT], fys[RS::NPT];
+        S.load(mod.g, g);
+        S.load(mod.n2, n2);
+        S.load(mod.car, cr);
+        S.load(px, fxs);
+        S.load(py, fys);
+        S.load(c0, c0s);
         fuse_ring(mod.bout, A.nx, A.ny, ti, tj, FT);
 #pragma unroll
         for (int k = 0; k < RF::NPT; ++k) u[k] = F.ok[k] ? u[k] : cplx<T>{};
         RF::put(u, s1);  // s1 was last read before the last barrier of the chain
         __syncthreads();
-        fuse_demod<RF, T>(F, i0, j0, mod, s1, car, g, n2, XH, RW - 1 - XH, RW, kv[0]);
+        fuse_demod<RW, RS, T>(S, n0, m0, mod, s1 + RF::S0 + (H - HN) * (RW + 1), cr, g, n2, kv[0]);
+        S.coefs(A, fxs, fys, c0s);
 #pragma unroll
-        for (int k = 0; k < RF::NPT; ++k)
-            if (RF::in(k, H, H + FT - 1) && F.ok[k]) st_off(mod.bout, F.p[k], kv[0][k]);
-        F.template chain<3>(kv, s0, s1);
-        F.gram(kv, H, H + FT - 1, red, part_out);
+        for (int k = 0; k < RS::NPT; ++k)
+            if (RS::in(k, HN, HN + FT - 1) && S.ok[k]) st_off(mod.bout, S.p[k], kv[0][k]);
+        S.template chain<3>(kv, s0, s1);
+        S.gram(kv, HN, HN + FT - 1, red, part_out);
     }
 }
 
