@@ -136,7 +136,7 @@ static void batch_free(helm_batch b) {
 // FGMRES(restart) in lockstep: per iteration one launch per kernel for every problem
 // still iterating, with each problem's own Krylov scalars, Givens rotations, stopping
 // test and iteration count, so that each problem goes through exactly the operations of
-// its single solve (helm_solve mode 1) and gives the same result bit for bit.
+// a single solve on its context (helm_solve mode 1) and gives the same result bit for bit.
 static constexpr int CLASS_GATHER = 2 * (MAXM + 2);  // doubles gathered per problem and column
 
 static bool same_desc(const helm_desc& a, const helm_desc& b) { return std::memcmp(&a, &b, sizeof(helm_desc)) == 0; }
@@ -180,6 +180,7 @@ static helm_ctx class_build(helm_batch_s::Class& K, int q, const helm_desc& d, c
     c->d = desc_normalized(d);
     c->arena = K.arena + (size_t)q * K.stride;
     c->arena_cap = K.stride;
+    c->sharing = (int)K.probs.size();
     try {
         build(c, velocity, st);
         ensure_solver_ws(c, 1);

@@ -144,6 +144,7 @@ struct helm_ctx_s {
     // in allocation order (its region of a batch class); count_bytes sums every allocation
     char* arena = nullptr;
     size_t arena_cap = 0, arena_used = 0, count_bytes = 0;
+    int sharing = 1;  // problems of its batch class, which share its launches (a launch shape like tn)
     void* bg = nullptr;  // batch staging of g and u (complex128, fine grid)
     void* bu = nullptr;
     helm::KrylovScal* Kout = nullptr;
@@ -685,11 +686,12 @@ struct Engine {
     // Levels l..LA run so: GMRES(3) on every one of them, none in a form set by a tuning, at
     // least two levels, and level l of at most FUSE_FOLD tiles of 32 x 32 (one per CU; a
     // larger level is bound by its arithmetic, of which the rings recompute up to 2.5 times).
+    // Nor are those of a large batch class, whose launches fill the chip (FUSE_SHARED).
     bool fuse_levels(int l) const {
         if (c->d.gmres_m != 3 || c->d.gmres_coarse_m != 3 || c->d.gmres_arnoldi || c->LA <= l) return false;
         for (int q = l; q <= c->LA; ++q)
             if (c->tn.sstep_rows[q] != 0) return false;
-        return fuse_tiles(c->al[l].nx, c->al[l].ny, 32) <= FUSE_FOLD;
+        return fuse_tiles(c->al[l].nx, c->al[l].ny, 32) <= FUSE_FOLD && c->sharing * fuse_ng(l) <= FUSE_SHARED;
     }
     // Tile edge of the kernels whose finer level is l: 16 x 16 while that gives at most one
     // block per CU and partials that the consumers can sum (FUSE_FOLD), else 32 x 32.

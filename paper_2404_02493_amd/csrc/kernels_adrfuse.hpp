@@ -35,6 +35,12 @@ namespace helm {
 // Up to this many partials every block of the consumer sums the Gram partials and solves
 // the normal equations itself (at most 32 KiB of partials per block).
 constexpr int FUSE_FOLD = 256;
+// Up to this many blocks of all problems of a batch class together (five per CU) the levels
+// are joined.  Beyond, the launches that joining saves no longer count and the rings that it
+// recomputes do.  Twenty iterations of a class, joined | separate passes: eight problems of
+// 512^2 (256 tiles each) 26 ms | 20 (from 12 and 20 problems), of 1024^2 (256) 52 | 44; twenty
+// of 512^2 59 | 41, of 1024^2 130 | 100, of 256^2 (64) 18.7 | about 20.
+constexpr int FUSE_SHARED = 1280;
 
 __host__ __device__ inline int fuse_side(int m, int ft) { return (m - 2) / ft + 1; }
 __host__ __device__ inline int fuse_tiles(int nx, int ny, int ft) { return fuse_side(nx, ft) * fuse_side(ny, ft); }

@@ -42,3 +42,32 @@ def test_joined_adr_levels(ny, nx, levels, adr_levels, prec):
         H.cycle(gd, ud)
         assert_close(ud, ref, TOL[prec], f"cycle {rep}")
     H.close()
+
+
+def test_separate_passes_of_a_large_class():
+    """40 problems of 256^2 (64 tiles each, more than five blocks per CU together) take separate
+    passes: solves equal those on the same contexts, and a context's cycle the oracle's."""
+    from oracle.cycle import Problem
+    from paper_2404_02493_amd import HelmholtzBatch
+
+    cases = [hi.make_problem(256, 0.5 * 256, 5, seed=31 + p, medium="grf", phase="fmm", damping_cells=8)
+             for p in range(2)]
+    B = HelmholtzBatch([dict(velocity=c.velocity, k=c.k, levels=c.levels, damping_cells=c.damping_cells, phi=c.phi)
+                        for c in cases * 20], precision="c64", lanes=1)
+    gs = [torch.as_tensor(c.g).to("cuda:0") for c in cases * 20]
+    us, its, rr, st = B.solve(gs, tol=1e-6, maxit=400, mode=1)
+    torch.cuda.synchronize()
+    assert np.all(st == 0) and np.all(rr < 1e-6) and np.all(B.classes() == B.classes()[0])
+    for p in (0, 39):
+        u, it, r, _ = B.problem(p).solve(gs[p], tol=1e-6, maxit=400, mode=1)
+        assert it == its[p] and r == rr[p] and torch.equal(u, us[p])
+    c = cases[0]
+    H = B.problem(0)
+    P = Problem(c.velocity, c.k, c.levels, damping_cells=c.damping_cells, phi=c.phi)
+    H.set_weights(P.weights.numpy())
+    u = rounded(rand_grid(np.random.default_rng(3), (256, 256)), H.cdtype)
+    g = rounded(torch.as_tensor(c.g), H.cdtype)
+    ud = to_dev(u, H.cdtype)
+    H.cycle(to_dev(g, H.cdtype), ud)
+    assert_close(ud, cycle(P, g, u), TOL["c64"], "cycle")
+    B.close()
