@@ -161,7 +161,10 @@ helm_status helm_eikonal(helm_ctx ctx, const double* src_xy, int32_t nsrc, int32
 
 /* Per-level smoother weights (host, `levels` doubles): w[0] = damped-Jacobi weight
  * of level 1 (Section 3.1.1), w[l-1] = Chebyshev interval parameter alpha_l of
- * level l >= 2 (eq. cheb; interval [lambda_l/alpha_l, lambda_l]).  alpha_l >= 1. */
+ * level l >= 2 (eq. cheb; interval [lambda_l/alpha_l, lambda_l]).  alpha_l >= 1.
+ * Waits for the context's queued cycles, recordings and reverses, which still take the
+ * weights before, whatever their stream (replays of a graph that the caller captured
+ * from them are not tracked). */
 helm_status helm_set_weights(helm_ctx ctx, const double* w);
 helm_status helm_get_weights(helm_ctx ctx, double* w);
 /* Upper end lambda_l of the Chebyshev interval (eq. cheb), the Gershgorin bound of the

@@ -139,6 +139,7 @@ struct helm_ctx_s {
     size_t partials_cap = 0;  // doubles
     double* dscal = nullptr;  // small device scratch (norms)
     helm::CycleDev* cdev = nullptr;  // Chebyshev tables and level (lambda, alpha) on the device
+    hipEvent_t cdev_read = nullptr;  // behind the last queued call that reads cdev (queued_read)
     helm::BatchIdx bi{};             // problems served by each launch (zero: this context alone)
     // batch arena: the context's device buffers are carved from [arena, arena + arena_cap)
     // in allocation order (its region of a batch class); count_bytes sums every allocation
@@ -1331,6 +1332,23 @@ static void write_cycle_tables(helm_ctx c) {
     HIPCHK(hipMemcpy(c->cdev, &h, offsetof(CycleDev, lv) + (c->L + 1) * sizeof(CycleDev::Level), hipMemcpyHostToDevice));
 }
 
+// Marks st behind work that reads the tables and that the host does not wait for:
+// helm_set_weights takes no stream, so it waits for this event before it rewrites them.  The
+// null stream needs none (the tables' hipMemcpy is queued behind it; an event costs 4.7 us
+// of a 311 us cycle), and a stream under capture is left alone (its replays are the caller's
+// to order).
+static void queued_read(helm_ctx c, hipStream_t st) {
+    if (st == nullptr) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (cap != hipStreamCaptureStatusNone) return;
+    if (!c->cdev_read) HIPCHK(hipEventCreateWithFlags(&c->cdev_read, hipEventDisableTiming));
+    HIPCHK(hipEventRecord(c->cdev_read, st));
+}
+
 // ------------------------------------------------------------------ setup
 // The descriptor a context keeps: ny = n for a square grid given with ny = 0.
 static helm_desc desc_normalized(const helm_desc& d) {
@@ -1973,6 +1991,7 @@ helm_status helm_set_weights(helm_ctx ctx, const double* w) {
             REQUIRE(std::isfinite(w[l]), "weights must be finite");
             if (l >= 1) REQUIRE(w[l] >= 1.0, "Chebyshev alpha must be >= 1");
         }
+        if (ctx->cdev_read) HIPCHK(hipEventSynchronize(ctx->cdev_read));
         ctx->w.assign(w, w + ctx->L);
         write_cycle_tables(ctx);  // captured graphs read the weights from there
         ++ctx->data_gen;
@@ -2003,6 +2022,7 @@ helm_status helm_cycle(helm_ctx ctx, const void* g, void* u, void* stream) {
             throw Error(HELM_ESTATE, "helm_set_phase must be called before helm_cycle");
         cycle_any(ctx, g, u, u, (hipStream_t)stream);
         HIPCHK(hipGetLastError());
+        queued_read(ctx, (hipStream_t)stream);
         return HELM_OK;
     })
 }
@@ -2068,6 +2088,7 @@ helm_status helm_cycle_backward(helm_ctx ctx, int32_t K, const void* g, const vo
         if (ctx->f32) cycle_backward<float>(ctx, K, g, u0, grad_uK, grad_phi, grad_w, ckpt_ws, st);
         else cycle_backward<double>(ctx, K, g, u0, grad_uK, grad_phi, grad_w, ckpt_ws, st);
         HIPCHK(hipGetLastError());
+        queued_read(ctx, st);
         return HELM_OK;
     })
 }
@@ -2085,6 +2106,7 @@ helm_status helm_cycle_record(helm_ctx ctx, int32_t K, const void* g, const void
             throw Error(HELM_ENOMEM, "helm_cycle_record: the K tapes do not fit (helm_cycle_backward records "
                                      "one cycle at a time)");
         HIPCHK(hipGetLastError());
+        queued_read(ctx, st);
         return HELM_OK;
     })
 }
@@ -2107,6 +2129,7 @@ helm_status helm_cycle_reverse(helm_ctx ctx, int32_t K, const void* g, const voi
         if (ctx->f32) cycle_reverse<float>(ctx, grad_uK, grad_phi, grad_w, st);
         else cycle_reverse<double>(ctx, grad_uK, grad_phi, grad_w, st);
         HIPCHK(hipGetLastError());
+        queued_read(ctx, st);
         return HELM_OK;
     })
 }
@@ -2576,6 +2599,7 @@ helm_status helm_destroy(helm_ctx ctx) {
     delete ctx->adj;
     ctx->adj = nullptr;
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
+    if (ctx->cdev_read) (void)hipEventDestroy(ctx->cdev_read);
     for (hipEvent_t e : ctx->prof.pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : ctx->col_ev)
         if (e) (void)hipEventDestroy(e);
