@@ -131,17 +131,19 @@ static std::string tune_ctx(helm_ctx c, hipStream_t st) {
             }
             c->tn.sstep_rows[l] = best;
             // levels l..LA joined across their Gram passes (every one at its default form)
-            if (l > 2 || c->phase_set) {
-                const helm_ctx_s::Tuning chosen = c->tn;
-                for (int q = l; q <= c->LA && q < 16; ++q) c->tn.sstep_rows[q] = 0;
-                bool joined = E.fuse_levels(l);
-                if (joined) {
-                    const double t = timed();
-                    note("sstep_l" + std::to_string(l) + "_joined", t);
-                    joined = t < tbest;
-                }
-                if (!joined) c->tn = chosen;
+            const helm_ctx_s::Tuning chosen = c->tn;
+            for (int q = l; q <= c->LA && q < 16; ++q) c->tn.sstep_rows[q] = 0;
+            bool joined = E.fuse_levels(l);
+            if (joined && l == 2 && !c->phase_set) {
+                // joined steps need a phase to be timed: nothing was compared with them, so level 2
+                // keeps the default, unless the levels below it took a form that they cannot join
+                for (int q = 3; q <= c->LA && q < 16; ++q) joined = joined && chosen.sstep_rows[q] == 0;
+            } else if (joined) {
+                const double t = timed();
+                note("sstep_l" + std::to_string(l) + "_joined", t);
+                joined = t < tbest;
             }
+            if (!joined) c->tn = chosen;
         }
     }
     // outer FGMRES passes on the fine grid (basis of the inner solver for complex64
