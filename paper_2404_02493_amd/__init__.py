@@ -260,7 +260,7 @@ class Helmholtz:
         size = f"n={self.n}" if self.ny == self.n else f"n={self.n}x{self.ny}"
         return (f"{name}|{size}|L={self.levels}|{'c64' if self.cdtype == torch.complex64 else 'c128'}"
                 f"|m={d.gmres_m}/{d.gmres_coarse_m}|adr={d.adr_levels}|tail={d.tail_n}|arnoldi={d.gmres_arnoldi}"
-                f"|restart={d.restart}|v4")
+                f"|restart={d.restart}|v5")  # v5: the joined form of the ADR levels is a candidate
 
     def tune(self, cache: str | None = None, stream=None) -> dict:
         """Chooses launch shapes by measurement (helm_tune) and applies them.  With a

@@ -1,7 +1,7 @@
 """The joined form of the ADR levels as a candidate of the tuner (stored as no entry): it is timed
 wherever it applies and the fastest timing of each level is what is stored; a context tuned
-before it has a phase does not lose it; where levels cannot be joined, a form is stored for
-each.
+before it has a phase, and one with a cache file from before the form was a candidate, do
+not lose it; where levels cannot be joined, a form is stored for each.
 """
 import json
 import re
@@ -84,6 +84,18 @@ def test_tuned_before_the_phase(case):
     ud = to_dev(u, H.cdtype)
     H.cycle(to_dev(g, H.cdtype), ud)
     assert_close(ud, cycle(P, g, u), TOL["c64"], "cycle")
+    H.close()
+
+
+def test_old_cache_is_measured_again(case, tmp_path):
+    """A cache file written when the joined form was no candidate does not bar it."""
+    H = _context(case)
+    old = re.sub(r"\|v\d+$", "|v4", H.tuning_key())
+    path = tmp_path / "tune.json"
+    path.write_text(json.dumps({old: {"sstep_rows": {"2": 1, "3": 1}, "fgmres_blocks": 512}}))
+    res = H.tune(cache=str(path))
+    assert "sstep_l2_joined" in res["timings_ms"]
+    assert json.loads(path.read_text())[H.tuning_key()] == res
     H.close()
 
 
