@@ -389,7 +389,7 @@ def batch_measure(seed: int, lanes: int, tol: float, maxit: int, steps: int = 1,
     import torch
 
     import helm_inputs as hi
-    from paper_2404_02493_amd import HelmholtzBatch
+    from paper_2404_02493_amd import Helmholtz, HelmholtzBatch
 
     t = time.perf_counter()
     cases = hi.make_batch(seed)
@@ -406,10 +406,12 @@ def batch_measure(seed: int, lanes: int, tol: float, maxit: int, steps: int = 1,
         torch.cuda.synchronize()
         log(f"lanes={nl}: setup of {len(cases)} contexts in {time.perf_counter() - t:.1f} s")
         if not per_size:
-            # one problem of each size alone: untuned default shapes, then the tuner's choice
+            # one problem of each size alone, on a context of its own (those of the batch take the
+            # launch shapes of their class): untuned default shapes, then the tuner's choice
             for n in sizes:
-                p = next(q for q, c in enumerate(cases) if c.n == n)
-                P = B.problem(p)
+                p, c = next((q, c) for q, c in enumerate(cases) if c.n == n)
+                P = Helmholtz(c.velocity, c.k, levels=c.levels, precision="c64", damping_cells=c.damping_cells)
+                P.set_phase(c.phi)
                 per_size[str(n)] = {"problems": sum(1 for c in cases if c.n == n)}
                 for label in (("default", "tuned") if tune else ("default",)):
                     if label == "tuned":
@@ -429,7 +431,7 @@ def batch_measure(seed: int, lanes: int, tol: float, maxit: int, steps: int = 1,
                         "iterations": its1, "seconds_profiled": round(dt, 4), "kernel_ms": round(ms, 3),
                         "algorithmic_GBs_in_kernels": round(by / (ms * 1e-3) / 1e9, 1),
                         "kernel_busy_frac": round(ms * 1e-3 / dt, 3)}
-                P.set_tuning({"sstep_rows": {}, "fgmres_blocks": 0})
+                P.close()
         for w in range(warmup):
             B.solve(gs, tol=tol, maxit=maxit, mode=1)
         torch.cuda.synchronize()

@@ -292,8 +292,12 @@ helm_status helm_batch_solve(helm_batch b, const void* const* g, void* const* u,
  * (FP32 cycles, at most 64 per class) are built region by region in one arena at setup and
  * solved in lockstep: every kernel is launched once for all problems of the class still
  * iterating (gridDim.z of them), each problem keeping its own Krylov scalars, Givens
- * rotations, stopping test and iteration count, so that its result equals its single
- * solve bit for bit.  A class runs in lockstep only while its contexts have one phase and
+ * rotations, stopping test and iteration count, so that its result equals helm_solve on
+ * its own context (helm_batch_get) bit for bit.  Launch shapes follow the size of the
+ * class: with more than 1280 tiles of its problems together on an ADR level (six problems
+ * of 512^2 or 1024^2, 21 of 256^2) the levels are not joined, also when such a context is
+ * solved alone, and results equal those of a context from helm_setup up to rounding, not
+ * bit for bit.  A class runs in lockstep only while its contexts have one phase and
  * equal launch shapes; otherwise its problems run alone. */
 helm_status helm_batch_classes(helm_batch b, int32_t* class_of);
 helm_status helm_batch_destroy(helm_batch b); /* NULL-safe */
@@ -306,6 +310,8 @@ helm_status helm_batch_destroy(helm_batch b); /* NULL-safe */
  *   {"n": .., "levels": .., "prec": "c64"|"c128", "sstep_rows": {"<level>": form, ..},
  *    "fgmres_blocks": blocks, "timings_ms": {..}}
  * Only the split of FP64 partial sums changes, so results change at rounding level.
+ * Level 2 is timed in whole ADR steps when the phase is set; without one the form that
+ * joins the ADR levels cannot be timed and is kept where it is the default.
  * Synchronises the stream; overwrites the ADR work buffers (call it between cycles). */
 helm_status helm_tune(helm_ctx ctx, char* json, int64_t cap, void* stream);
 /* Applies a tuning JSON from helm_tune (a cached one); unknown keys are ignored,

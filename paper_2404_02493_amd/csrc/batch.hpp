@@ -6,8 +6,10 @@
 // problem from a shared queue ordered by decreasing node count (longest first), so the
 // small, launch-bound coarse levels of one problem overlap with the kernels of
 // the others.  Every problem runs exactly the kernels and launch shapes of a
-// single helm_solve on its own context, so its result equals the single solve
-// bit for bit.  Per-problem convergence is tracked on the host (status, iters,
+// single helm_solve on its own context (helm_batch_get), so its result equals that
+// solve bit for bit.  Those shapes follow the size of its class (Engine::fuse_levels): a
+// context of a large class takes the separate ADR passes also when it is solved alone,
+// and equals a context from helm_setup, which joins them, up to rounding.  Per-problem convergence is tracked on the host (status, iters,
 // relres); a converged problem leaves its lane to the next one.
 //
 // Included from helm.hip inside namespace helm.
