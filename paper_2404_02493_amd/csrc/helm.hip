@@ -145,7 +145,9 @@ struct helm_ctx_s {
     // in allocation order (its region of a batch class); count_bytes sums every allocation
     char* arena = nullptr;
     size_t arena_cap = 0, arena_used = 0, count_bytes = 0;
-    int sharing = 1;  // problems of its batch class, which share its launches (a launch shape like tn)
+    // problems of its batch class, whose launches it shares: a launch shape like tn, fixed at setup
+    // so that every solve on the context, in the class or alone, takes the same passes
+    int sharing = 1;
     void* bg = nullptr;  // batch staging of g and u (complex128, fine grid)
     void* bu = nullptr;
     helm::KrylovScal* Kout = nullptr;
@@ -493,7 +495,7 @@ struct Engine {
     using ChebType = std::conditional_t<FT <= 32, double, T>;
     bool cheb_passes() const { return c->d.cheb_pre <= CHEBM && c->d.cheb_post <= CHEBM; }
     // f(tile edge) for level l: 16 while that is at most one block per CU, then 32, then 64 in
-    // FP32 (134 KB of LDS, one block per CU: a level of 1024^2 is one wave of 256 blocks).
+    // FP32 (117 KB of LDS, one block per CU: a level of 1024^2 is one wave of 256 blocks).
     template <typename F>
     void with_cheb_edge(int l, F&& f) const {
         const int nx = c->wl[l].nx, ny = c->wl[l].ny;
@@ -711,7 +713,7 @@ struct Engine {
             const double bytes = (3 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny) + (2 * sizeof(C) + 2 * sizeof(T)) * NN2(B.nx, B.ny);
             with_edge(fuse_ft(q), [&](auto e) {
                 constexpr int FT = decltype(e)::value;
-                LAUNCH(c, bytes, (k_fuse_down<T, FT>), dim3(fuse_ng(q)), dim3(FuseCfg<T, FT>::DOWN), st, A.A, B.A,
+                LAUNCH(c, bytes, (k_fuse_down<T, FT>), dim3(fuse_ng(q)), dim3(FuseCfg<FT>::DOWN), st, A.A, B.A,
                        (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b, (const double*)fuse_part(h), np,
                        (C*)A.x, (const T*)B.px, (const T*)B.py, (const C*)B.c0, (C*)B.b, fuse_part(1 - h));
             });
@@ -735,7 +737,7 @@ struct Engine {
         auto go = [&](auto xc, auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, bytes, (k_fuse_up<T, decltype(xc)::value, FT, GRAM>), dim3(fuse_tiles(A.nx, A.ny, FT)),
-                   dim3(FuseCfg<T, FT>::UP), st, A.A, B.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   dim3(FuseCfg<FT>::UP), st, A.A, B.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
                    (const C*)(GRAM ? A.x : pinto), (C*)(GRAM ? A.xalt : pinto), (const T*)B.px, (const T*)B.py,
                    (const C*)B.c0, (const C*)B.b, (const C*)B.x, (const double*)fuse_part(h), np, fuse_part(1 - h));
         };
@@ -771,7 +773,7 @@ struct Engine {
         with_edge(fuse_ft(l), [&](auto e) {
             constexpr int FT = decltype(e)::value;
             LAUNCH(c, (2 * sizeof(C) + 2 * sizeof(T)) * NN2(A.nx, A.ny), (k_fuse_gram<T, FT>), dim3(fuse_ng(l)),
-                   dim3(FuseCfg<T, FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
+                   dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, (const C*)A.b,
                    fuse_part(h));
         });
         fuse_down_up(l, h);
@@ -790,14 +792,14 @@ struct Engine {
         int h = 0;
         with_edge(fuse_ft(2), [&](auto e) {
             constexpr int FT = decltype(e)::value;
-            LAUNCH(c, (5 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_start<T, FT>), dim3(ng), dim3(FuseCfg<T, FT>::START), st,
+            LAUNCH(c, (5 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_start<T, FT>), dim3(ng), dim3(FuseCfg<FT>::START), st,
                    A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0, mod_args(nullptr, A.b), fuse_part(h));
             for (int s = 0; s < M; ++s) {
                 fuse_down_up(2, h);
                 if (s + 1 < M) {
                     const ModArgs<T> ma = mod_args(W.u == u_home ? W.ualt : u_home, A.b == b_home ? A.balt : b_home);
                     LAUNCH(c, (9 * sizeof(C) + 3 * sizeof(T)) * nn, (k_fuse_step<T, true, FT>), dim3(ng),
-                           dim3(FuseCfg<T, FT>::STEP), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           dim3(FuseCfg<FT>::STEP), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
                            (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, fuse_part(1 - h));
                     std::swap(W.u, W.ualt);
                     std::swap(A.b, A.balt);
@@ -805,7 +807,7 @@ struct Engine {
                 } else {
                     const ModArgs<T> ma = mod_args(u_home, nullptr);
                     LAUNCH(c, (6 * sizeof(C) + 2 * sizeof(T)) * nn, (k_fuse_step<T, false, FT>), dim3(ng),
-                           dim3(FuseCfg<T, FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
+                           dim3(FuseCfg<FT>::LAST), st, A.A, (const T*)A.px, (const T*)A.py, (const C*)A.c0,
                            (const C*)A.b, (const C*)A.x, (const double*)fuse_part(h), ng, ma, (double*)nullptr);
                     if (W.u != u_home) std::swap(W.u, W.ualt);
                 }

@@ -6,9 +6,8 @@
 //   k_fuse_down   level l: x = pre-smoother, b_{l+1} = R (b - M x); Gram sums on l + 1
 //   k_fuse_up     level l: x += P x_{l+1}, x_{l+1} the finished smoother of level l + 1;
 //                 Gram sums of the post-smoother on l
-//   k_fuse_step   level 2: u += x e^{i theta}, x the finished post-smoother, and
-//                 k_fuse_start of the next ADR step
-//   k_fuse_last   level 2: u += x e^{i theta}
+//   k_fuse_step   level 2: u += x e^{i theta}, x the finished post-smoother, and, unless it is
+//                 the last ADR step, k_fuse_start of the next one
 // On levels of a few hundred nodes per side a pass is bound by its launch, one memory
 // round trip and the issue time of its vector instructions on the CUs that it occupies,
 // so recomputing the rings that the next operation needs costs less than the launches
@@ -37,9 +36,12 @@ namespace helm {
 constexpr int FUSE_FOLD = 256;
 // Up to this many blocks of all problems of a batch class together (five per CU) the levels
 // are joined.  Beyond, the launches that joining saves no longer count and the rings that it
-// recomputes do.  Twenty iterations of a class, joined | separate passes: eight problems of
-// 512^2 (256 tiles each) 26 ms | 20 (from 12 and 20 problems), of 1024^2 (256) 52 | 44; twenty
-// of 512^2 59 | 41, of 1024^2 130 | 100, of 256^2 (64) 18.7 | about 20.
+// recomputes do.  Twenty iterations of a class in ms, joined | separate passes, by its problems:
+//   512^2 (256 tiles of 16 x 16)    3: 12.5 | 21.2   5: 18.4 | 23.8   8: 26.2 | 26.9   20: 59 | 41
+//   1024^2 (256 tiles of 32 x 32)   3: 22.2 | 23.0   5: 34.4 | 31.7   8: 52.2 | 44.6   20: 130 | 100
+//   256^2 (64 tiles of 16 x 16)     8: 10.4 | 17.6   20: 18.7 | about 20
+// The two edges cross at about eight and between three and four problems; the one line lies
+// between, at five of either.
 constexpr int FUSE_SHARED = 1280;
 
 __host__ __device__ inline int fuse_side(int m, int ft) { return (m - 2) / ft + 1; }
@@ -50,18 +52,18 @@ __host__ __device__ inline int fuse_tiles(int nx, int ny, int ft) { return fuse_
 // and four nodes a thread) keep them free of spills (FP64 on 512^2: DOWN with 896 threads
 // of three nodes spilled 36 registers, 21.3 us against 11.8; STEP with 768 spilled 20, 18.4
 // against 15.2; FP32 the same within 0.3 us).
-template <typename T, int FT>
+template <int FT>
 struct FuseCfg;
-template <typename T>
-struct FuseCfg<T, 16> {
+template <>
+struct FuseCfg<16> {
     static constexpr int DOWN = 640, UP = 576, START = 576, STEP = 960, LAST = 512;
 };
-template <typename T>
-struct FuseCfg<T, 32> {
+template <>
+struct FuseCfg<32> {
     static constexpr int DOWN = 512, UP = 832, START = 832, STEP = 512, LAST = 768;
 };
-template <typename T>
-struct FuseCfg<T, 64> {  // k_fuse_up without Gram sums only
+template <>
+struct FuseCfg<64> {  // k_fuse_up without Gram sums only
     static constexpr int UP = 768;
 };
 
@@ -266,13 +268,13 @@ __device__ __forceinline__ void fuse_ring(cplx<T>* __restrict__ x, int nx, int n
 // K_0 - sum_j c_j K_j) on the coarse tile and a ring of 3, K_0..K_3 of the coarse
 // smoother there and its Gram sums.  fuse_tiles(A.nx, A.ny, FT) blocks.
 template <typename T, int FT>
-__global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
+__global__ __launch_bounds__((FuseCfg<FT>::DOWN)) void k_fuse_down(
     AdrGeom A, AdrGeom Ac, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const double* __restrict__ part_in, int ng, cplx<T>* __restrict__ xout,
     const T* __restrict__ pxc, const T* __restrict__ pyc, const cplx<T>* __restrict__ c0c, cplx<T>* __restrict__ bc,
     double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, part_in, xout, pxc, pyc, c0c, bc, part_out);
-    constexpr int FB = FuseCfg<T, FT>::DOWN, TC = FT / 2;
+    constexpr int FB = FuseCfg<FT>::DOWN, TC = FT / 2;
     constexpr int HC = 3, RC = TC + 2 * HC;          // coarse region
     constexpr int OF = 2 * HC + 2, RW = 2 * RC + 5;  // fine region of K_1.., the tile at OF
     using RO = FuseOuter<T, RW, FB>;                 // and of K_0
@@ -356,13 +358,13 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::DOWN)) void k_fuse_down(
 // Gram sums of the pre-smoother on the first joined level when that is not level 2.
 // fuse_tiles(A.nx, A.ny, FT) blocks.
 template <typename T, int FT>
-__global__ __launch_bounds__((FuseCfg<T, FT>::LAST)) void k_fuse_gram(AdrGeom A, const T* __restrict__ px,
+__global__ __launch_bounds__((FuseCfg<FT>::LAST)) void k_fuse_gram(AdrGeom A, const T* __restrict__ px,
                                                                  const T* __restrict__ py,
                                                                  const cplx<T>* __restrict__ c0,
                                                                  const cplx<T>* __restrict__ b,
                                                                  double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, part_out);
-    constexpr int FB = FuseCfg<T, FT>::LAST, H = 3, RW = FT + 2 * H;
+    constexpr int FB = FuseCfg<FT>::LAST, H = 3, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
     __shared__ cplx<T> buf[2 * RF::LB];
     __shared__ double red[FB / 64 * 16];
@@ -387,14 +389,14 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::LAST)) void k_fuse_gram(AdrGeom A,
 // fuse_tiles(A.nx, A.ny, FT) blocks; with GRAM xout must not overlap xin (without, the two
 // are one array and xout's ring is left alone).
 template <typename T, bool X0C, int FT, bool GRAM>
-__global__ __launch_bounds__((FuseCfg<T, FT>::UP)) void k_fuse_up(
+__global__ __launch_bounds__((FuseCfg<FT>::UP)) void k_fuse_up(
     AdrGeom A, AdrGeom Ac, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const cplx<T>* __restrict__ xin, cplx<T>* __restrict__ xout,
     const T* __restrict__ pxc, const T* __restrict__ pyc, const cplx<T>* __restrict__ c0c,
     const cplx<T>* __restrict__ bc, const cplx<T>* __restrict__ xc, const double* __restrict__ part_in, int ng,
     double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, xin, xout, pxc, pyc, c0c, bc, xc, part_in, part_out);
-    constexpr int FB = FuseCfg<T, FT>::UP, TC = FT / 2;
+    constexpr int FB = FuseCfg<FT>::UP, TC = FT / 2;
     constexpr int H = GRAM ? 4 : 0, RW = FT + 2 * H;  // fine region: fine node 1 + FT ti - H + r
     constexpr int HC = X0C ? 3 : 2, RC = TC + H + 1 + 2 * HC;  // coarse node TC ti - H / 2 - HC + r
     using RF = FuseReg<T, RW, FB>;
@@ -503,12 +505,12 @@ __device__ __forceinline__ void fuse_demod(const RF& R, int i0, int j0, const Mo
 // First ADR step of a cycle: the demodulated residual and the Gram sums of the
 // pre-smoother on level 2.  mod.u read, mod.bout written.
 template <typename T, int FT>
-__global__ __launch_bounds__((FuseCfg<T, FT>::START)) void k_fuse_start(AdrGeom A, const T* __restrict__ px,
+__global__ __launch_bounds__((FuseCfg<FT>::START)) void k_fuse_start(AdrGeom A, const T* __restrict__ px,
                                                                    const T* __restrict__ py,
                                                                    const cplx<T>* __restrict__ c0, ModArgs<T> mod,
                                                                    double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, mod, part_out);
-    constexpr int FB = FuseCfg<T, FT>::START, H = 3, RW = FT + 2 * H;
+    constexpr int FB = FuseCfg<FT>::START, H = 3, RW = FT + 2 * H;
     using RF = FuseReg<T, RW, FB>;
     using RO = FuseOuter<T, RW, FB>;
     constexpr int LB = RO::N > RF::LB ? RO::N : RF::LB;
@@ -546,12 +548,12 @@ __global__ __launch_bounds__((FuseCfg<T, FT>::START)) void k_fuse_start(AdrGeom 
 // also the demodulated residual of the next ADR step and the Gram sums of its
 // pre-smoother (x on the tile and a ring of 4, the residual on a ring of 3).
 template <typename T, bool NEXT, int FT>
-__global__ __launch_bounds__((NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST)) void k_fuse_step(
+__global__ __launch_bounds__((NEXT ? FuseCfg<FT>::STEP : FuseCfg<FT>::LAST)) void k_fuse_step(
     AdrGeom A, const T* __restrict__ px, const T* __restrict__ py, const cplx<T>* __restrict__ c0,
     const cplx<T>* __restrict__ b, const cplx<T>* __restrict__ x0, const double* __restrict__ part_in, int ng,
     ModArgs<T> mod, double* __restrict__ part_out, BatchIdx bi) {
     bshift(bi.off(), px, py, c0, b, x0, part_in, mod, part_out);
-    constexpr int FB = NEXT ? FuseCfg<T, FT>::STEP : FuseCfg<T, FT>::LAST;
+    constexpr int FB = NEXT ? FuseCfg<FT>::STEP : FuseCfg<FT>::LAST;
     constexpr int XH = NEXT ? 4 : 0, H = 2 + XH, RW = FT + 2 * H;  // region of r = b - M x0
     constexpr int HN = 3, RN = FT + 2 * HN;                        // and of the next right-hand side
     using RF = FuseReg<T, RW, FB>;
