@@ -22,7 +22,10 @@ template <bool ZERO>
 constexpr int FINE_DOWN = ZERO ? 640 : 704;
 constexpr int FINE_UP = 640;
 
-// (w / d) v at node k, by one reciprocal of |d|^2 (FP32: the hardware's, corrected once)
+// (w / d) v at node k, by one reciprocal of |d|^2 (FP32: the hardware's, corrected once): a
+// rounding more than by divisions.  Error of the two passes alone against FP64 from a nonzero start
+// (512^2, FP32): 5.37e-8, with divisions 5.29e-8 (from zero 5.19e-8, where the row marches have
+// 8.4e-8); a whole cycle's is 3e-7 to 6e-7.
 template <typename R, typename T>
 __device__ __forceinline__ cplx<T> fine_sweep(const R& F, int k, T w, cplx<T> v) {
     const T dr = T(4) * F.l[k] - F.kp[k].re, di = -F.kp[k].im, D = dr * dr + di * di;
